@@ -421,7 +421,8 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
     int xa, xe;
     bool out;          // the own site is in the output region (in y and z)
     bool in_i;         // the own site is in I (in y and z); the flux there is not zero
-    bool yz_near;      // an output site within two sites of a y or z face of I
+    // uniform over the wave: it has an output site within two sites of a y face / of a z face of I
+    bool wave_y_near, wave_z_near;
     unsigned outside;  // bit d: the y/z neighbour d (O_* below) lies outside I
     enum : unsigned { O_YP1 = 1, O_YM1 = 2, O_YP2 = 4, O_YM2 = 8, O_ZP1 = 16, O_ZM1 = 32, O_ZP2 = 64, O_ZM2 = 128 };
 
@@ -474,39 +475,55 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
         outside = (y + 1 > hy ? O_YP1 : 0u) | (y - 1 < ly ? O_YM1 : 0u) | (y + 2 > hy ? O_YP2 : 0u) |
                   (y - 2 < ly ? O_YM2 : 0u) | (z + 1 > hz ? O_ZP1 : 0u) | (z - 1 < lz ? O_ZM1 : 0u) |
                   (z + 2 > hz ? O_ZP2 : 0u) | (z - 2 < lz ? O_ZM2 : 0u);
-        yz_near = out && outside != 0u;
+        wave_y_near = __builtin_amdgcn_ballot_w64(out && (outside & (O_YP1 | O_YM1 | O_YP2 | O_YM2))) != 0;
+        wave_z_near = __builtin_amdgcn_ballot_w64(out && (outside & (O_ZP1 | O_ZM1 | O_ZP2 | O_ZM2))) != 0;
         off = cm.site_off(y, z);
         xa = s.xa;
         xe = s.xe;
     }
 
+    // The terms of Lap phi whose neighbour lies outside I, from the neighbours read for the
+    // derivatives.  Every axis is a branch of its own, taken only by waves with a site within two
+    // of a face of that axis: the tiles at the z faces run the z terms on every plane and are the
+    // last blocks of a launch to end, so they must not pay for the other axes as well (four
+    // selects and two sums per component against sixteen and ten).  Measured: the double sweep
+    // of 256^3 505 -> 482 us, of 40^3 50.2 -> 47.4; the float one of 96^3 with the sextic term 55 -> 52.
     template <int SM2, int SM1, int S0, int SP1, int SP2>
-    __device__ __forceinline__ void boundary_terms(int j, const Site4<T>* P)
+    __device__ __forceinline__ void boundary_terms(int j, bool x_near, const T (&Ym2)[4], const T (&Ym1)[4],
+                                                   const T (&Yp1)[4], const T (&Yp2)[4], const T (&Zm2)[4],
+                                                   const T (&Zm1)[4], const T (&Zp1)[4], const T (&Zp2)[4])
     {
-        if (!out) return;
-        const int lx = cm.ilo[0], hx = cm.ihi[0];
-        const T* pa0 = P[pidx].v;
-        constexpr int W = 4 * G::PW;  // one row of sites, in elements
+        const auto pick = [](bool c, T v) { return c ? v : T(0); };
+        T o1[4], o2[4];  // sums of the outside first / second neighbours
 #pragma unroll
-        for (int A = 0; A < 4; ++A) {
-            const T* pa = pa0 + A;
-            T o1 = T(0), o2 = T(0);  // outside first / second neighbours
-            if (j + 1 > hx) o1 += ring[SP1][A];
-            if (j - 1 < lx) o1 += ring[SM1][A];
-            if (j + 2 > hx) o2 += ring[SP2][A];
-            if (j - 2 < lx) o2 += ring[SM2][A];
-            if (outside & O_YP1) o1 += pa[W];
-            if (outside & O_YM1) o1 += pa[-W];
-            if (outside & O_ZP1) o1 += pa[4];
-            if (outside & O_ZM1) o1 += pa[-4];
-            if (outside & O_YP2) o2 += pa[2 * W];
-            if (outside & O_YM2) o2 += pa[-2 * W];
-            if (outside & O_ZP2) o2 += pa[8];
-            if (outside & O_ZM2) o2 += pa[-8];
-            // + 1/2 the outside terms of Lap phi: 12 h^2 x that is 8 o1 - o2 / 2, and L^ enters
-            // the scaled gradient with weight lapw < 0 and the opposite sign
-            acc[S0][A] = fmaT(k.lapw, fmaT(T(0.5), o2, T(-8) * o1), acc[S0][A]);
+        for (int A = 0; A < 4; ++A) o1[A] = o2[A] = T(0);
+        if (x_near) {
+            const int lx = cm.ilo[0], hx = cm.ihi[0];
+#pragma unroll
+            for (int A = 0; A < 4; ++A) {
+                o1[A] = pick(j + 1 > hx, ring[SP1][A]) + pick(j - 1 < lx, ring[SM1][A]);
+                o2[A] = pick(j + 2 > hx, ring[SP2][A]) + pick(j - 2 < lx, ring[SM2][A]);
+            }
         }
+        if (wave_y_near) {
+#pragma unroll
+            for (int A = 0; A < 4; ++A) {
+                o1[A] = (o1[A] + pick(outside & O_YP1, Yp1[A])) + pick(outside & O_YM1, Ym1[A]);
+                o2[A] = (o2[A] + pick(outside & O_YP2, Yp2[A])) + pick(outside & O_YM2, Ym2[A]);
+            }
+        }
+        if (wave_z_near) {
+#pragma unroll
+            for (int A = 0; A < 4; ++A) {
+                o1[A] = (o1[A] + pick(outside & O_ZP1, Zp1[A])) + pick(outside & O_ZM1, Zm1[A]);
+                o2[A] = (o2[A] + pick(outside & O_ZP2, Zp2[A])) + pick(outside & O_ZM2, Zm2[A]);
+            }
+        }
+        // + 1/2 the outside terms of Lap phi: 12 h^2 x that is 8 o1 - o2 / 2, and L^ enters the
+        // scaled gradient with weight lapw < 0 and the opposite sign (zero at sites without such
+        // neighbours, and unused outside the output region)
+#pragma unroll
+        for (int A = 0; A < 4; ++A) acc[S0][A] = fmaT(k.lapw, fmaT(T(0.5), o2[A], T(-8) * o1[A]), acc[S0][A]);
     }
 
     template <int U> __device__ __forceinline__ void step(int j, int pb)
@@ -588,7 +605,8 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
         // whose neighbour lies outside I count half.  Only sites within two of a face of I
         // have such terms; a wave none of whose sites has one skips this.
         const bool x_near = (j <= cm.ilo[0] + 1) || (j >= cm.ihi[0] - 1);
-        if (j_out && (x_near || __builtin_amdgcn_ballot_w64(yz_near) != 0)) boundary_terms<SM2, SM1, S0, SP1, SP2>(j, P);
+        if (j_out && (x_near || wave_y_near || wave_z_near))
+            boundary_terms<SM2, SM1, S0, SP1, SP2>(j, x_near, Ym2, Ym1, Yp1, Yp2, Zm2, Zm1, Zp1, Zp2);
 
         const T gxx = dot4(ax, ax), gyy = dot4(ay, ay), gzz = dot4(az, az);
         const T gxy = dot4(ax, ay), gxz = dot4(ax, az), gyz = dot4(ay, az);
