@@ -53,8 +53,8 @@ using FpGeoF64 = FpGeo<4, 32>;
 template <typename T> using FpGeoOf = std::conditional_t<sizeof(T) == 4, FpGeoF32, FpGeoF64>;
 
 template <typename T, class G> struct FormPSmem {
-    Site4<T> phi[4][G::PPLANE];  // [plane mod 4][site]
-    Site4<T> dz[3][G::ZPLANE];   // 12 h D_z phi, [plane mod 3][site]
+    SitePlane<T, G::PPLANE> phi[4];  // [plane mod 4]
+    SitePlane<T, G::ZPLANE> dz[3];   // 12 h D_z phi, [plane mod 3]
     double red[G::NW][NPART];
     int last;  // this block is the last of the sweep to finish
 };
@@ -199,9 +199,9 @@ template <typename T, int MODE, bool EXT> struct FormP {
             asm volatile("" : "+v"(axz[sl][0]), "+v"(axz[sl][1]), "+v"(axz[sl][2]), "+v"(axz[sl][3]));
         }
         // stage plane s into the buffer of plane s-4 (its last reads came before the last barrier)
-        Site4<T>* B = sm.phi[s & 3];
-        st4(B + pidx, nxt);
-        if (floader) st4(B + fidx, fnxt);
+        auto& B = sm.phi[s & 3];
+        B.st(pidx, nxt);
+        if (floader) B.st(fidx, fnxt);
 #pragma unroll
         for (int A = 0; A < 4; ++A) ring[Q0][A] = nxt[A];
         // the velocity of output plane s-2 was prefetched one step earlier; plane s-1's now
@@ -227,29 +227,27 @@ template <typename T, int MODE, bool EXT> struct FormP {
         // t = s+1, -1 at t = s-2 and +1 at t = s+2; D_z phi also goes to the plane's D_z
         // buffer (whose y-differences give D_y D_z phi two steps later), with that of the
         // frame sites in the rows above and below the tile
-        Site4<T>* Z = sm.dz[s % 3];
+        auto& Z = sm.dz[s % 3];
         if (fdz) {
-            const Site4<T>* F = B + fidx;
             T m2[4], m1[4], p1[4], p2[4], d[4];
-            ld4(F - 2, m2);
-            ld4(F - 1, m1);
-            ld4(F + 1, p1);
-            ld4(F + 2, p2);
+            B.ld(fidx - 2, m2);
+            B.ld(fidx - 1, m1);
+            B.ld(fidx + 1, p1);
+            B.ld(fidx + 2, p2);
 #pragma unroll
             for (int A = 0; A < 4; ++A) d[A] = d1s(m2[A], m1[A], p1[A], p2[A]);
-            st4(Z + fzidx, d);
+            Z.st(fzidx, d);
         }
         {
-            const Site4<T>* P = B + pidx;
             T ym2[4], ym1[4], yp1[4], yp2[4], zm2[4], zm1[4], zp1[4], zp2[4];
-            ld4(P - 2 * G::PW, ym2);
-            ld4(P - G::PW, ym1);
-            ld4(P + G::PW, yp1);
-            ld4(P + 2 * G::PW, yp2);
-            ld4(P - 2, zm2);
-            ld4(P - 1, zm1);
-            ld4(P + 1, zp1);
-            ld4(P + 2, zp2);
+            B.ld(pidx - 2 * G::PW, ym2);
+            B.ld(pidx - G::PW, ym1);
+            B.ld(pidx + G::PW, yp1);
+            B.ld(pidx + 2 * G::PW, yp2);
+            B.ld(pidx - 2, zm2);
+            B.ld(pidx - 1, zm1);
+            B.ld(pidx + 1, zp1);
+            B.ld(pidx + 2, zp2);
             T azs[4];
 #pragma unroll
             for (int A = 0; A < 4; ++A) {
@@ -265,7 +263,7 @@ template <typename T, int MODE, bool EXT> struct FormP {
                 axz[Q2][A] -= az;
                 axz[Q3][A] += az;
             }
-            st4(Z + zidx, azs);
+            Z.st(zidx, azs);
         }
 
         const int t = s - 2;
@@ -281,18 +279,18 @@ template <typename T, int MODE, bool EXT> struct FormP {
     // the accumulators of plane t (slot Q2) are complete
     template <int Q4, int Q3, int Q2, int Q1, int Q0> __device__ __forceinline__ void finish(int t, const T (&vcur)[4])
     {
-        const Site4<T>* P = sm.phi[t & 3] + pidx;
+        const auto& P = sm.phi[t & 3];
         T c[4], ax[4], ay[4], az[4], dxx[4], dyy[4], dzz[4], dyz[4], lap[4];
         {
             T ym2[4], ym1[4], yp1[4], yp2[4], zm2[4], zm1[4], zp1[4], zp2[4];
-            ld4(P - 2 * G::PW, ym2);
-            ld4(P - G::PW, ym1);
-            ld4(P + G::PW, yp1);
-            ld4(P + 2 * G::PW, yp2);
-            ld4(P - 2, zm2);
-            ld4(P - 1, zm1);
-            ld4(P + 1, zp1);
-            ld4(P + 2, zp2);
+            P.ld(pidx - 2 * G::PW, ym2);
+            P.ld(pidx - G::PW, ym1);
+            P.ld(pidx + G::PW, yp1);
+            P.ld(pidx + 2 * G::PW, yp2);
+            P.ld(pidx - 2, zm2);
+            P.ld(pidx - 1, zm1);
+            P.ld(pidx + 1, zp1);
+            P.ld(pidx + 2, zp2);
 #pragma unroll
             for (int A = 0; A < 4; ++A) {
                 const T cc = ring[Q2][A];
@@ -308,12 +306,12 @@ template <typename T, int MODE, bool EXT> struct FormP {
         }
         {
             // D~_yz: the y-difference of the D_z phi plane (written two steps earlier)
-            const Site4<T>* Z = sm.dz[t % 3] + zidx;
+            const auto& Z = sm.dz[t % 3];
             T m2[4], m1[4], p1[4], p2[4];
-            ld4(Z - 2 * G::OZ, m2);
-            ld4(Z - G::OZ, m1);
-            ld4(Z + G::OZ, p1);
-            ld4(Z + 2 * G::OZ, p2);
+            Z.ld(zidx - 2 * G::OZ, m2);
+            Z.ld(zidx - G::OZ, m1);
+            Z.ld(zidx + G::OZ, p1);
+            Z.ld(zidx + 2 * G::OZ, p2);
 #pragma unroll
             for (int A = 0; A < 4; ++A) dyz[A] = d1s(m2[A], m1[A], p1[A], p2[A]);
         }

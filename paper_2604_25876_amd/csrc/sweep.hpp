@@ -252,30 +252,33 @@ __device__ __forceinline__ T det4_cofactors(const T* c0, const T* c1, const T* c
 __device__ __forceinline__ float fmaT(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmaT(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// The four components of a site, contiguous in LDS: one 16-byte (float) or two
-// 16-byte (double) LDS accesses per site.
-template <typename T> struct alignas(4 * sizeof(T)) Site4 {
-    T v[4];
-};
-template <typename T> __device__ __forceinline__ void ld4(const Site4<T>* p, T (&o)[4])
-{
-    if constexpr (sizeof(T) == 4) {
-        const float4 t = *(const float4*)p;
+// A plane of N sites of four components in LDS.  Every access moves 16 bytes per lane with
+// neighbouring lanes 16 bytes apart: one for a float site; two for a double site, whose
+// component pairs lie in two arrays.  (Whole 32-byte records put the lanes of one access 32
+// bytes apart, on half of the banks: 53% of the LDS cycles of the double sweep were conflicts.)
+template <typename T, int N> struct SitePlane;
+template <int N> struct SitePlane<float, N> {
+    float4 s[N];
+    __device__ __forceinline__ void ld(int i, float (&o)[4]) const
+    {
+        const float4 t = s[i];
         o[0] = t.x, o[1] = t.y, o[2] = t.z, o[3] = t.w;
-    } else {
-        const double2 a = *(const double2*)p, b = *((const double2*)p + 1);
+    }
+    __device__ __forceinline__ void st(int i, const float (&v)[4]) { s[i] = make_float4(v[0], v[1], v[2], v[3]); }
+};
+template <int N> struct SitePlane<double, N> {
+    double2 s[2][N];
+    __device__ __forceinline__ void ld(int i, double (&o)[4]) const
+    {
+        const double2 a = s[0][i], b = s[1][i];
         o[0] = a.x, o[1] = a.y, o[2] = b.x, o[3] = b.y;
     }
-}
-template <typename T> __device__ __forceinline__ void st4(Site4<T>* p, const T (&i)[4])
-{
-    if constexpr (sizeof(T) == 4) {
-        *(float4*)p = make_float4(i[0], i[1], i[2], i[3]);
-    } else {
-        *(double2*)p = make_double2(i[0], i[1]);
-        *((double2*)p + 1) = make_double2(i[2], i[3]);
+    __device__ __forceinline__ void st(int i, const double (&v)[4])
+    {
+        s[0][i] = make_double2(v[0], v[1]);
+        s[1][i] = make_double2(v[2], v[3]);
     }
-}
+};
 
 // Tile geometry of a shape: NWI interior waves of 64 / OZ rows of OZ lanes, NWH halo
 // waves whose lanes hold HPT halo positions each.
@@ -301,8 +304,8 @@ template <int NWI_, int NWH_, int HPT_, int OZ_> struct Geo {
 };
 
 template <typename T, class G> struct SweepSmem {
-    Site4<T> phi[2][G::PPLANE];     // [plane parity][site]
-    Site4<T> q[2][2][G::QPLANE];    // [plane parity][0: Q_y, 1: Q_z][site]
+    SitePlane<T, G::PPLANE> phi[2];     // [plane parity]
+    SitePlane<T, 2 * G::QPLANE> q[2];   // [plane parity]: sites of Q_y, then those of Q_z
     double red[G::NW][NPART];
     int last;  // this block is the last of its field to finish the sweep
 };
@@ -539,7 +542,7 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
             asm volatile("" : "+v"(ring[sl][0]), "+v"(ring[sl][1]), "+v"(ring[sl][2]), "+v"(ring[sl][3]));
         // stage phi(j+1) into the other phi buffer (its last reads, of phi(j-1), came before
         // the last barrier), then prefetch
-        st4(&sm.phi[qb][pidx], ring[SP1]);
+        sm.phi[qb].st(pidx, ring[SP1]);
         // the velocity of output plane j-2 was prefetched one plane earlier; the velocity of
         // plane j-1 is loaded now, before the prefetch of phi(j+3) (loads complete in order)
         T vcur[4];
@@ -563,17 +566,17 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
         const bool j_in = (j >= cm.ilo[0]) && (j <= cm.ihi[0]);
         const bool j_out = (j >= xa) && (j < xe);
 
-        const Site4<T>* P = sm.phi[pb];
+        const auto& P = sm.phi[pb];
         T c[4], ax[4], ay[4], az[4];
         T Ym2[4], Ym1[4], Yp1[4], Yp2[4], Zm2[4], Zm1[4], Zp1[4], Zp2[4];
-        ld4(P + pidx - 2 * G::PW, Ym2);
-        ld4(P + pidx - G::PW, Ym1);
-        ld4(P + pidx + G::PW, Yp1);
-        ld4(P + pidx + 2 * G::PW, Yp2);
-        ld4(P + pidx - 2, Zm2);
-        ld4(P + pidx - 1, Zm1);
-        ld4(P + pidx + 1, Zp1);
-        ld4(P + pidx + 2, Zp2);
+        P.ld(pidx - 2 * G::PW, Ym2);
+        P.ld(pidx - G::PW, Ym1);
+        P.ld(pidx + G::PW, Yp1);
+        P.ld(pidx + 2 * G::PW, Yp2);
+        P.ld(pidx - 2, Zm2);
+        P.ld(pidx - 1, Zm1);
+        P.ld(pidx + 1, Zp1);
+        P.ld(pidx + 2, Zp2);
         T cl = T(0);
 #pragma unroll
         for (int A = 0; A < 4; ++A) {
@@ -640,8 +643,8 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
                 e6 = k.c6e * det * det;
             }
         }
-        st4(&sm.q[pb][0][qidx], qy);
-        st4(&sm.q[pb][1][qidx], qz);
+        sm.q[pb].st(qidx, qy);
+        sm.q[pb].st(qidx + G::QPLANE, qz);
 #pragma unroll
         for (int A = 0; A < 4; ++A) {
             // x-divergence pushed to the accumulators of planes j-2 .. j+2
@@ -667,17 +670,17 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
 
         // y- and z-divergence of the flux of plane j-1 (written before the last barrier)
         if (j - 1 >= xa && j - 1 < xe) {
-            const Site4<T>* fy = sm.q[qb][0] + qidx;
-            const Site4<T>* fz = sm.q[qb][1] + qidx;
+            const auto& F = sm.q[qb];
+            const int fz = qidx + G::QPLANE;
             T ym2[4], ym1[4], yp1[4], yp2[4], zm2[4], zm1[4], zp1[4], zp2[4];
-            ld4(fy - 2 * G::QW, ym2);
-            ld4(fy - G::QW, ym1);
-            ld4(fy + G::QW, yp1);
-            ld4(fy + 2 * G::QW, yp2);
-            ld4(fz - 2, zm2);
-            ld4(fz - 1, zm1);
-            ld4(fz + 1, zp1);
-            ld4(fz + 2, zp2);
+            F.ld(qidx - 2 * G::QW, ym2);
+            F.ld(qidx - G::QW, ym1);
+            F.ld(qidx + G::QW, yp1);
+            F.ld(qidx + 2 * G::QW, yp2);
+            F.ld(fz - 2, zm2);
+            F.ld(fz - 1, zm1);
+            F.ld(fz + 1, zp1);
+            F.ld(fz + 2, zp2);
 #pragma unroll
             for (int A = 0; A < 4; ++A) {
                 const T t = (ym1[A] - yp1[A]) + (zm1[A] - zp1[A]);
@@ -768,7 +771,7 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
 #pragma unroll
             for (int A = 0; A < 4; ++A) vnxt[A] = ldb_nt((gptr<const T>)cm.vel[A], vb + off);
         }
-        st4(&sm.phi[0][pidx], ring[2]);
+        sm.phi[0].st(pidx, ring[2]);
         __syncthreads();
         const int nst = (xe - xa) + 4 + lead;
         for (int st = 0; st < nst; st += 5) {
@@ -878,7 +881,7 @@ template <typename T, class G, bool FROM_TABLE, int EXT> struct Halo {
     {
         constexpr int SM2 = U % 5, SM1 = (U + 1) % 5, S0 = (U + 2) % 5, SP1 = (U + 3) % 5, SP2 = (U + 4) % 5;
         const int qb = pb ^ 1;
-        Site4<T>* Pn = sm.phi[qb];
+        auto& Pn = sm.phi[qb];
 #pragma unroll
         for (int i = 0; i < HPT; ++i) {
             asm volatile("" : "+v"(pidx[i]), "+v"(qidx[i]), "+v"(off[i]));
@@ -886,7 +889,7 @@ template <typename T, class G, bool FROM_TABLE, int EXT> struct Halo {
             for (int sl = 0; sl < 5; ++sl)
                 asm volatile("" : "+v"(ring[i][sl][0]), "+v"(ring[i][sl][1]), "+v"(ring[i][sl][2]), "+v"(ring[i][sl][3]));
             // stage phi(j+1) into the other phi buffer, then prefetch
-            if (active[i]) st4(Pn + pidx[i], ring[i][SP1]);
+            if (active[i]) Pn.st(pidx[i], ring[i][SP1]);
 #pragma unroll
             for (int A = 0; A < 4; ++A) ring[i][SP2][A] = nxt[i][A];
             if (active[i]) cm.load(off[i], j + 3, nxt[i]);
@@ -896,27 +899,27 @@ template <typename T, class G, bool FROM_TABLE, int EXT> struct Halo {
         for (int i = 0; i < FPT; ++i) {
             asm volatile("" : "+v"(fidx[i]), "+v"(foff[i]));
             if (floader[i]) {
-                st4(Pn + fidx[i], fnxt[i]);
+                Pn.st(fidx[i], fnxt[i]);
                 cm.load(foff[i], j + 2, fnxt[i]);
             }
         }
         const bool j_in = (j >= cm.ilo[0]) && (j <= cm.ihi[0]);
-        const Site4<T>* P = sm.phi[pb];
+        const auto& P = sm.phi[pb];
 #pragma unroll
         for (int i = 0; i < HPT; ++i) {
             if (!active[i]) continue;
             T c[4], ax[4], ap[4], aq[4];
             const bool yh = is_y[i];
             T Ym2[4], Ym1[4], Yp1[4], Yp2[4], Zm2[4], Zm1[4], Zp1[4], Zp2[4];
-            const Site4<T>* pa = P + pidx[i];
-            ld4(pa - 2 * G::PW, Ym2);
-            ld4(pa - G::PW, Ym1);
-            ld4(pa + G::PW, Yp1);
-            ld4(pa + 2 * G::PW, Yp2);
-            ld4(pa - 2, Zm2);
-            ld4(pa - 1, Zm1);
-            ld4(pa + 1, Zp1);
-            ld4(pa + 2, Zp2);
+            const int pa = pidx[i];
+            P.ld(pa - 2 * G::PW, Ym2);
+            P.ld(pa - G::PW, Ym1);
+            P.ld(pa + G::PW, Yp1);
+            P.ld(pa + 2 * G::PW, Yp2);
+            P.ld(pa - 2, Zm2);
+            P.ld(pa - 1, Zm1);
+            P.ld(pa + 1, Zp1);
+            P.ld(pa + 2, Zp2);
 #pragma unroll
             for (int A = 0; A < 4; ++A) {
                 c[A] = ring[i][S0][A];
@@ -948,7 +951,7 @@ template <typename T, class G, bool FROM_TABLE, int EXT> struct Halo {
                     for (int A = 0; A < 4; ++A) qp[A] = fmaT(dv, yh ? C2[A] : C3[A], qp[A]);
                 }
             }
-            st4(sm.q[pb][0] + qidx[i], qp);
+            sm.q[pb].st(qidx[i], qp);
         }
         __syncthreads();
     }
@@ -966,11 +969,11 @@ template <typename T, class G, bool FROM_TABLE, int EXT> struct Halo {
             cm.load(off[i], js + 1, ring[i][3]);
             cm.load(off[i], js + 2, nxt[i]);
         }
-        Site4<T>* Q = sm.phi[0];
+        auto& Q = sm.phi[0];
 #pragma unroll
         for (int i = 0; i < HPT; ++i) {
             if (!active[i]) continue;
-            st4(Q + pidx[i], ring[i][2]);
+            Q.st(pidx[i], ring[i][2]);
         }
 #pragma unroll
         for (int i = 0; i < FPT; ++i) {
@@ -978,7 +981,7 @@ template <typename T, class G, bool FROM_TABLE, int EXT> struct Halo {
             T f0[4];
             cm.load(foff[i], js, f0);
             cm.load(foff[i], js + 1, fnxt[i]);
-            st4(Q + fidx[i], f0);
+            Q.st(fidx[i], f0);
         }
         __syncthreads();
         const int nst = (xe - xa) + 4 + lead;
