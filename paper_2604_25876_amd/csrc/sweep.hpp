@@ -419,7 +419,10 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
     const SweepConst<T>& k;
     const SweepCommon<T, FROM_TABLE>& cm;
     int row, col;
-    int pidx, qidx;    // LDS index of the own site in a phi plane and in a flux plane
+    // LDS index of the site two rows above the own one in a phi plane and in a flux plane: every
+    // neighbour then lies at a non-negative constant offset, which the access itself adds
+    int pidx, qidx;
+    static constexpr int PO = 2 * G::PW, QO = 2 * G::QW;  // the own site from there
     unsigned off;      // byte offset of the own site within a plane
     int xa, xe;
     bool out;          // the own site is in the output region (in y and z)
@@ -443,8 +446,8 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
     {
         row = tid / G::OZ;
         col = tid - row * G::OZ;
-        pidx = (row + 4) * G::PW + col + 4;
-        qidx = (row + 2) * G::QW + col + 2;
+        pidx = (row + 2) * G::PW + col + 4;
+        qidx = row * G::QW + col + 2;
     }
 
     __device__ __forceinline__ T potential(T p0) const
@@ -542,7 +545,7 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
             asm volatile("" : "+v"(ring[sl][0]), "+v"(ring[sl][1]), "+v"(ring[sl][2]), "+v"(ring[sl][3]));
         // stage phi(j+1) into the other phi buffer (its last reads, of phi(j-1), came before
         // the last barrier), then prefetch
-        sm.phi[qb].st(pidx, ring[SP1]);
+        sm.phi[qb].st(pidx + PO, ring[SP1]);
         // the velocity of output plane j-2 was prefetched one plane earlier; the velocity of
         // plane j-1 is loaded now, before the prefetch of phi(j+3) (loads complete in order)
         T vcur[4];
@@ -569,14 +572,14 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
         const auto& P = sm.phi[pb];
         T c[4], ax[4], ay[4], az[4];
         T Ym2[4], Ym1[4], Yp1[4], Yp2[4], Zm2[4], Zm1[4], Zp1[4], Zp2[4];
-        P.ld(pidx - 2 * G::PW, Ym2);
-        P.ld(pidx - G::PW, Ym1);
-        P.ld(pidx + G::PW, Yp1);
-        P.ld(pidx + 2 * G::PW, Yp2);
-        P.ld(pidx - 2, Zm2);
-        P.ld(pidx - 1, Zm1);
-        P.ld(pidx + 1, Zp1);
-        P.ld(pidx + 2, Zp2);
+        P.ld(pidx + (PO - 2 * G::PW), Ym2);
+        P.ld(pidx + (PO - G::PW), Ym1);
+        P.ld(pidx + (PO + G::PW), Yp1);
+        P.ld(pidx + (PO + 2 * G::PW), Yp2);
+        P.ld(pidx + (PO - 2), Zm2);
+        P.ld(pidx + (PO - 1), Zm1);
+        P.ld(pidx + (PO + 1), Zp1);
+        P.ld(pidx + (PO + 2), Zp2);
         T cl = T(0);
 #pragma unroll
         for (int A = 0; A < 4; ++A) {
@@ -588,21 +591,21 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
             ax[A] = fmaT(T(8), xp1 - xm1, xm2 - xp2);
             ay[A] = fmaT(T(8), yp1 - ym1, ym2 - yp2);
             az[A] = fmaT(T(8), zp1 - zm1, zm2 - zp2);
-            if (j_out) {
-                T lap;  // 12 h^2 Lap phi
-                if constexpr (sizeof(T) == 4) {
-                    // differences from the centre: no cancellation of O(1) terms in single precision
-                    const T s1 = ((xp1 - cc) + (xm1 - cc)) + ((yp1 - cc) + (ym1 - cc)) + ((zp1 - cc) + (zm1 - cc));
-                    const T s2 = ((xp2 - cc) + (xm2 - cc)) + ((yp2 - cc) + (ym2 - cc)) + ((zp2 - cc) + (zm2 - cc));
-                    lap = fmaT(T(16), s1, -s2);
-                } else {
-                    const T s1 = ((xp1 + xm1) + (yp1 + ym1)) + (zp1 + zm1);
-                    const T s2 = ((xp2 + xm2) + (yp2 + ym2)) + (zp2 + zm2);
-                    lap = fmaT(T(-90), cc, fmaT(T(16), s1, -s2));
-                }
-                cl = fmaT(cc, lap, cl);
-                acc[S0][A] = fmaT(k.lapw, lap, acc[S0][A]);
+            // (formed on every plane of the march: beside the output planes it reaches no
+            // accumulator that is read)
+            T lap;  // 12 h^2 Lap phi
+            if constexpr (sizeof(T) == 4) {
+                // differences from the centre: no cancellation of O(1) terms in single precision
+                const T s1 = ((xp1 - cc) + (xm1 - cc)) + ((yp1 - cc) + (ym1 - cc)) + ((zp1 - cc) + (zm1 - cc));
+                const T s2 = ((xp2 - cc) + (xm2 - cc)) + ((yp2 - cc) + (ym2 - cc)) + ((zp2 - cc) + (zm2 - cc));
+                lap = fmaT(T(16), s1, -s2);
+            } else {
+                const T s1 = ((xp1 + xm1) + (yp1 + ym1)) + (zp1 + zm1);
+                const T s2 = ((xp2 + xm2) + (yp2 + ym2)) + (zp2 + zm2);
+                lap = fmaT(T(-90), cc, fmaT(T(16), s1, -s2));
             }
+            cl = fmaT(cc, lap, cl);
+            acc[S0][A] = fmaT(k.lapw, lap, acc[S0][A]);
         }
         // The E2 part of the gradient is -1/2 (Lap phi + Lap(1_I phi)): the terms of Lap phi
         // whose neighbour lies outside I count half.  Only sites within two of a face of I
@@ -643,8 +646,8 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
                 e6 = k.c6e * det * det;
             }
         }
-        sm.q[pb].st(qidx, qy);
-        sm.q[pb].st(qidx + G::QPLANE, qz);
+        sm.q[pb].st(qidx + QO, qy);
+        sm.q[pb].st(qidx + (QO + G::QPLANE), qz);
 #pragma unroll
         for (int A = 0; A < 4; ++A) {
             // x-divergence pushed to the accumulators of planes j-2 .. j+2
@@ -671,16 +674,15 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
         // y- and z-divergence of the flux of plane j-1 (written before the last barrier)
         if (j - 1 >= xa && j - 1 < xe) {
             const auto& F = sm.q[qb];
-            const int fz = qidx + G::QPLANE;
             T ym2[4], ym1[4], yp1[4], yp2[4], zm2[4], zm1[4], zp1[4], zp2[4];
-            F.ld(qidx - 2 * G::QW, ym2);
-            F.ld(qidx - G::QW, ym1);
-            F.ld(qidx + G::QW, yp1);
-            F.ld(qidx + 2 * G::QW, yp2);
-            F.ld(fz - 2, zm2);
-            F.ld(fz - 1, zm1);
-            F.ld(fz + 1, zp1);
-            F.ld(fz + 2, zp2);
+            F.ld(qidx + (QO - 2 * G::QW), ym2);
+            F.ld(qidx + (QO - G::QW), ym1);
+            F.ld(qidx + (QO + G::QW), yp1);
+            F.ld(qidx + (QO + 2 * G::QW), yp2);
+            F.ld(qidx + (QO + G::QPLANE - 2), zm2);
+            F.ld(qidx + (QO + G::QPLANE - 1), zm1);
+            F.ld(qidx + (QO + G::QPLANE + 1), zp1);
+            F.ld(qidx + (QO + G::QPLANE + 2), zp2);
 #pragma unroll
             for (int A = 0; A < 4; ++A) {
                 const T t = (ym1[A] - yp1[A]) + (zm1[A] - zp1[A]);
@@ -771,7 +773,7 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
 #pragma unroll
             for (int A = 0; A < 4; ++A) vnxt[A] = ldb_nt((gptr<const T>)cm.vel[A], vb + off);
         }
-        sm.phi[0].st(pidx, ring[2]);
+        sm.phi[0].st(pidx + PO, ring[2]);
         __syncthreads();
         const int nst = (xe - xa) + 4 + lead;
         for (int st = 0; st < nst; st += 5) {
@@ -795,7 +797,7 @@ template <typename T, class G, bool FROM_TABLE, int EXT> struct Halo {
     const SweepConst<T>& k;
     const SweepCommon<T, FROM_TABLE>& cm;
     int pos[HPT];        // halo position index (>= NHALO: none)
-    int pidx[HPT];       // LDS index in a phi plane
+    int pidx[HPT];       // LDS index in a phi plane of the site two rows above
     int qidx[HPT];       // LDS index of the supplied flux (Q_y or Q_z plane, component 0)
     unsigned off[HPT];
     bool active[HPT], is_y[HPT], vyz[HPT];
@@ -834,7 +836,7 @@ template <typename T, class G, bool FROM_TABLE, int EXT> struct Halo {
             hr[i] = r;
             hc[i] = cc;
             is_y[i] = yh;
-            pidx[i] = (r + 4) * G::PW + cc + 4;
+            pidx[i] = (r + 2) * G::PW + cc + 4;
             qidx[i] = (yh ? 0 : G::QPLANE) + (r + 2) * G::QW + cc + 2;
         }
 #pragma unroll
@@ -889,7 +891,7 @@ template <typename T, class G, bool FROM_TABLE, int EXT> struct Halo {
             for (int sl = 0; sl < 5; ++sl)
                 asm volatile("" : "+v"(ring[i][sl][0]), "+v"(ring[i][sl][1]), "+v"(ring[i][sl][2]), "+v"(ring[i][sl][3]));
             // stage phi(j+1) into the other phi buffer, then prefetch
-            if (active[i]) Pn.st(pidx[i], ring[i][SP1]);
+            if (active[i]) Pn.st(pidx[i] + 2 * G::PW, ring[i][SP1]);
 #pragma unroll
             for (int A = 0; A < 4; ++A) ring[i][SP2][A] = nxt[i][A];
             if (active[i]) cm.load(off[i], j + 3, nxt[i]);
@@ -912,14 +914,14 @@ template <typename T, class G, bool FROM_TABLE, int EXT> struct Halo {
             const bool yh = is_y[i];
             T Ym2[4], Ym1[4], Yp1[4], Yp2[4], Zm2[4], Zm1[4], Zp1[4], Zp2[4];
             const int pa = pidx[i];
-            P.ld(pa - 2 * G::PW, Ym2);
-            P.ld(pa - G::PW, Ym1);
-            P.ld(pa + G::PW, Yp1);
-            P.ld(pa + 2 * G::PW, Yp2);
-            P.ld(pa - 2, Zm2);
-            P.ld(pa - 1, Zm1);
-            P.ld(pa + 1, Zp1);
-            P.ld(pa + 2, Zp2);
+            P.ld(pa + (2 * G::PW - 2 * G::PW), Ym2);
+            P.ld(pa + (2 * G::PW - G::PW), Ym1);
+            P.ld(pa + (2 * G::PW + G::PW), Yp1);
+            P.ld(pa + (2 * G::PW + 2 * G::PW), Yp2);
+            P.ld(pa + (2 * G::PW - 2), Zm2);
+            P.ld(pa + (2 * G::PW - 1), Zm1);
+            P.ld(pa + (2 * G::PW + 1), Zp1);
+            P.ld(pa + (2 * G::PW + 2), Zp2);
 #pragma unroll
             for (int A = 0; A < 4; ++A) {
                 c[A] = ring[i][S0][A];
@@ -973,7 +975,7 @@ template <typename T, class G, bool FROM_TABLE, int EXT> struct Halo {
 #pragma unroll
         for (int i = 0; i < HPT; ++i) {
             if (!active[i]) continue;
-            Q.st(pidx[i], ring[i][2]);
+            Q.st(pidx[i] + 2 * G::PW, ring[i][2]);
         }
 #pragma unroll
         for (int i = 0; i < FPT; ++i) {
