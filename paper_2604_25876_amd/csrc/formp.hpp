@@ -184,6 +184,22 @@ template <typename T, int MODE, bool EXT> struct FormP {
         return v;
     }
 
+    // Loads of a plane.  Each component's base is formed by the scalar unit at its use: the bases of
+    // four arrays' components, kept over the march, did not fit the scalar registers and came back
+    // from vector registers lane by lane.
+    __device__ __forceinline__ void load(unsigned o, int x, T (&dst)[4]) const
+    {
+        const unsigned base = (unsigned)clampi(x, 0, cm.n0 - 1) * cm.plane_b;
+#pragma unroll
+        for (int A = 0; A < 4; ++A) dst[A] = ldb(cm.comp(cm.pin[0], A), base + o);
+    }
+    __device__ __forceinline__ void load_vel(int x)
+    {
+        const unsigned base = (unsigned)clampi(x, 0, cm.n0 - 1) * cm.plane_b;
+#pragma unroll
+        for (int A = 0; A < 4; ++A) vnxt[A] = ldb_nt((gptr<const T>)cm.comp(cm.vel[0], A), base + off);
+    }
+
     // step s of the march: stage plane s, push D_x of its D_y phi and D_z phi, finish plane s-2
     template <int U> __device__ __forceinline__ void step(int s)
     {
@@ -207,19 +223,16 @@ template <typename T, int MODE, bool EXT> struct FormP {
         // the velocity of output plane s-2 was prefetched one step earlier; plane s-1's now
         T vcur[4];
         if constexpr (MODE == MODE_STEP) {
-            const unsigned vb = (unsigned)clampi(s - 1, 0, cm.n0 - 1) * cm.plane_b;
 #pragma unroll
-            for (int A = 0; A < 4; ++A) {
-                vcur[A] = vnxt[A];
-                vnxt[A] = ldb_nt((gptr<const T>)cm.vel[A], vb + off);
-            }
+            for (int A = 0; A < 4; ++A) vcur[A] = vnxt[A];
+            load_vel(s - 1);
             if (cm.redo) {  // a redo sweep starts from zero velocity
 #pragma unroll
                 for (int A = 0; A < 4; ++A) vcur[A] = T(0);
             }
         }
-        cm.load(off, s + 1, nxt);
-        if (floader) cm.load(foff, s + 1, fnxt);
+        load(off, s + 1, nxt);
+        if (floader) load(foff, s + 1, fnxt);
         __syncthreads();
 
         // D_y phi and D_z phi of the own column in plane s, pushed into D_x of them:
@@ -355,7 +368,7 @@ template <typename T, int MODE, bool EXT> struct FormP {
             if (cm.restore) {
 #pragma unroll
                 for (int A = 0; A < 4; ++A)
-                    stb_nt(cm.vel[A], base, cm.restore == RESTORE_ZERO ? T(0) : fmaT(-k.dtK, f[A], vcur[A]));
+                    stb_nt(cm.comp(cm.vel[0], A), base, cm.restore == RESTORE_ZERO ? T(0) : fmaT(-k.dtK, f[A], vcur[A]));
                 return;
             }
             T v[4], q[4], pn[4];
@@ -381,13 +394,13 @@ template <typename T, int MODE, bool EXT> struct FormP {
             }
 #pragma unroll
             for (int A = 0; A < 4; ++A) {
-                stb_nt(cm.pout[A], base, pn[A]);
-                stb_nt(cm.vel[A], base, v[A]);
+                stb_nt(cm.comp(cm.pout[0], A), base, pn[A]);
+                stb_nt(cm.comp(cm.vel[0], A), base, v[A]);
             }
         } else {
             if (cm.has_grad) {
 #pragma unroll
-                for (int A = 0; A < 4; ++A) stb_nt(cm.gout[A], base, (cm.projected ? -f[A] : g[A]) * k.invK);
+                for (int A = 0; A < 4; ++A) stb_nt(cm.comp(cm.gout[0], A), base, (cm.projected ? -f[A] : g[A]) * k.invK);
             }
         }
     }
@@ -406,12 +419,10 @@ template <typename T, int MODE, bool EXT> struct FormP {
             }
         const int lead = march_lead(xa, xe);
         const int s0 = xa - 2 - lead;
-        cm.load(off, s0, nxt);
-        if (floader) cm.load(foff, s0, fnxt);
+        load(off, s0, nxt);
+        if (floader) load(foff, s0, fnxt);
         if constexpr (MODE == MODE_STEP) {
-            const unsigned vb = (unsigned)clampi(s0 - 2, 0, cm.n0 - 1) * cm.plane_b;
-#pragma unroll
-            for (int A = 0; A < 4; ++A) vnxt[A] = ldb_nt((gptr<const T>)cm.vel[A], vb + off);
+            load_vel(s0 - 2);
         }
         const int nst = (xe - xa) + 4 + lead;
         for (int st = 0; st < nst; st += 5) {
@@ -485,6 +496,7 @@ void formp_kernel(SweepArgs a)
             cm.vel[A] = (gptr<T>)(pvel ? pvel + A * N3 : nullptr);
             cm.gout[A] = (gptr<T>)(pgrad ? pgrad + A * N3 : nullptr);
         }
+        cm.cs = N3 * (long long)sizeof(T);
     }
     cm.has_grad = a.grad != nullptr;
     cm.projected = a.projected != 0;

@@ -391,6 +391,7 @@ template <typename T, bool FROM_TABLE> struct SweepCommon {
     gptr<T> pout[4];
     gptr<T> vel[4];
     gptr<T> gout[4];
+    long long cs;        // bytes from one component to the next
     int n0, n1, n2;
     int zlo, zhi;        // the columns of a row a load may touch
     int ilo[3], ihi[3];  // I in array coordinates
@@ -404,6 +405,16 @@ template <typename T, bool FROM_TABLE> struct SweepCommon {
         const unsigned base = (unsigned)clampi(x, 0, n0 - 1) * plane_b;
 #pragma unroll
         for (int A = 0; A < 4; ++A) dst[A] = ldb(pin[A], base + off);
+    }
+    // component A of an array with component 0 at base: formed on the scalar unit where it is used
+    // and kept there (see formp.hpp)
+    template <typename P> __device__ __forceinline__ P comp(P base, int A) const
+    {
+        long long c = cs;
+        asm volatile("" : "+s"(c));
+        unsigned long long u = (unsigned long long)base + (unsigned long long)(A * c);
+        asm volatile("" : "+s"(u));
+        return (P)u;
     }
     __device__ __forceinline__ unsigned site_off(int y, int z) const
     {
@@ -1167,6 +1178,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, S
             cm.vel[A] = (gptr<T>)(pvel ? pvel + A * N3 : nullptr);
             cm.gout[A] = (gptr<T>)(pgrad ? pgrad + A * N3 : nullptr);
         }
+        cm.cs = N3 * (long long)sizeof(T);
     }
     cm.has_grad = a.grad != nullptr;
     cm.projected = a.projected != 0;
