@@ -405,8 +405,7 @@ template <typename T, int MODE, bool EXT> struct FormP {
         }
     }
 
-    // the march over one segment: steps s = xa-2 .. xe+1 finish planes xa .. xe-1, in whole
-    // groups of five starting `lead` steps early (those reach no output plane)
+    // the march over one segment: steps s = xa-2 .. xe+1 finish planes xa .. xe-1
     __device__ __forceinline__ void march()
     {
 #pragma unroll
@@ -417,20 +416,23 @@ template <typename T, int MODE, bool EXT> struct FormP {
                 axz[sl][A] = T(0);
                 ring[sl][A] = T(0);
             }
-        const int lead = march_lead(xa, xe);
-        const int s0 = xa - 2 - lead;
+        const int s0 = xa - 2;
         load(off, s0, nxt);
         if (floader) load(foff, s0, fnxt);
         if constexpr (MODE == MODE_STEP) {
             load_vel(s0 - 2);
         }
-        const int nst = (xe - xa) + 4 + lead;
+        const int nst = (xe - xa) + 4;
         for (int st = 0; st < nst; st += 5) {
             const int s = s0 + st;
             step<0>(s);
+            if (st + 1 >= nst) break;
             step<1>(s + 1);
+            if (st + 2 >= nst) break;
             step<2>(s + 2);
+            if (st + 3 >= nst) break;
             step<3>(s + 3);
+            if (st + 4 >= nst) break;
             step<4>(s + 4);
         }
     }

@@ -380,10 +380,6 @@ __device__ __forceinline__ Segment item_segment(int item, int tiles, int tiles_z
     return s;
 }
 
-// A march over output planes [xa, xe) takes (xe - xa) + 4 steps (flux planes xa-2 ..
-// xe+1); it runs in whole groups of five and so starts this many planes early.
-__device__ __forceinline__ int march_lead(int xa, int xe) { return (5 - ((xe - xa) + 4) % 5) % 5; }
-
 // Fields, flags and sums shared by the two roles.
 template <typename T, bool FROM_TABLE> struct SweepCommon {
     // global-memory pointers, uniform over the block
@@ -770,10 +766,10 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
         for (int s = 0; s < 5; ++s)
 #pragma unroll
             for (int A = 0; A < 4; ++A) acc[s][A] = T(0);
-        // the march runs in groups of five planes; it starts `lead` planes early so that the
-        // last group ends with output plane xe-1 (the early planes reach no output plane)
-        const int lead = march_lead(xa, xe);
-        const int js = xa - 2 - lead;  // first flux plane; ring slots 0 .. 3 hold planes js-2 .. js+1
+        // The march is unrolled five planes deep and leaves the group at its last plane: rounding it
+        // up to whole groups cost two planes in the mean, 12% of a 16-plane slab (40^3 double, two
+        // 18-plane slabs: 47 -> 43.5 us).
+        const int js = xa - 2;  // first flux plane; ring slots 0 .. 3 hold planes js-2 .. js+1
         cm.load(off, js - 2, ring[0]);
         cm.load(off, js - 1, ring[1]);
         cm.load(off, js, ring[2]);
@@ -786,13 +782,17 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
         }
         sm.phi[0].st(pidx + PO, ring[2]);
         __syncthreads();
-        const int nst = (xe - xa) + 4 + lead;
+        const int nst = (xe - xa) + 4;
         for (int st = 0; st < nst; st += 5) {
             const int j = js + st, pb = st & 1;
             step<0>(j, pb);
+            if (st + 1 >= nst) break;
             step<1>(j + 1, pb ^ 1);
+            if (st + 2 >= nst) break;
             step<2>(j + 2, pb);
+            if (st + 3 >= nst) break;
             step<3>(j + 3, pb ^ 1);
+            if (st + 4 >= nst) break;
             step<4>(j + 4, pb);
         }
     }
@@ -971,8 +971,7 @@ template <typename T, class G, bool FROM_TABLE, int EXT> struct Halo {
 
     __device__ __forceinline__ void march()
     {
-        const int lead = march_lead(xa, xe);
-        const int js = xa - 2 - lead;
+        const int js = xa - 2;
 #pragma unroll
         for (int i = 0; i < HPT; ++i) {
             if (!active[i]) continue;
@@ -997,13 +996,17 @@ template <typename T, class G, bool FROM_TABLE, int EXT> struct Halo {
             Q.st(fidx[i], f0);
         }
         __syncthreads();
-        const int nst = (xe - xa) + 4 + lead;
+        const int nst = (xe - xa) + 4;
         for (int st = 0; st < nst; st += 5) {
             const int j = js + st, pb = st & 1;
             step<0>(j, pb);
+            if (st + 1 >= nst) break;
             step<1>(j + 1, pb ^ 1);
+            if (st + 2 >= nst) break;
             step<2>(j + 2, pb);
+            if (st + 3 >= nst) break;
             step<3>(j + 3, pb ^ 1);
+            if (st + 4 >= nst) break;
             step<4>(j + 4, pb);
         }
     }
