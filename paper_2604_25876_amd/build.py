@@ -4,12 +4,15 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 from pathlib import Path
 
 PKG = Path(__file__).resolve().parent
 ROOT = PKG.parent
-SOURCES = [PKG / "csrc" / "skyr.hip"]
-DEPS = SOURCES + [PKG / "csrc" / n for n in ("sweep.hpp", "shapes.hpp", "moments.hpp", "formp.hpp")] + \
+SOURCES = [PKG / "csrc" / n for n in ("skyr.hip", "kernels_step_f64.hip", "kernels_step_f32.hip",
+                                      "kernels_batch_f64.hip", "kernels_batch_f32.hip", "kernels_grad.hip")]
+DEPS = SOURCES + [PKG / "csrc" / n for n in ("sweep.hpp", "shapes.hpp", "kernels.hpp", "moments.hpp", "formp.hpp")] + \
     [ROOT / "include" / "skyr.h"]
 LIB = PKG / "libskyr.so"
 
@@ -22,13 +25,22 @@ HIPCC_FLAGS = [
 
 
 def build(verbose: bool = False, extra: list[str] | None = None) -> Path:
-    """Compile libskyr.so (always recompiles)."""
+    """Compile libskyr.so (always recompiles), its sources side by side."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIB.with_suffix(".so.tmp")
-    cmd = [hipcc, *HIPCC_FLAGS, *(extra or []), "-I", str(ROOT / "include"), "-o", str(tmp), *map(str, SOURCES)]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.check_call(cmd)
+
+    with tempfile.TemporaryDirectory() as d:
+        objects = [str(Path(d) / (s.stem + ".o")) for s in SOURCES]
+        compile_flags = [f for f in HIPCC_FLAGS if f != "-shared"] + list(extra or []) + ["-I", str(ROOT / "include")]
+        with ThreadPoolExecutor(min(len(SOURCES), os.cpu_count() or 1)) as pool:
+            list(pool.map(lambda so: run([hipcc, *compile_flags, "-c", str(so[0]), "-o", so[1]]),
+                          zip(SOURCES, objects)))
+        run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", str(tmp), *objects])
     os.replace(tmp, LIB)
     return LIB
 

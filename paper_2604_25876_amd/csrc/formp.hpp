@@ -24,7 +24,7 @@
 //     y/z second differences), the y-difference of its D_z phi plane (D_y D_z phi), the
 //     phi ring of its column (the x-differences) and the accumulators, complete by then;
 //   * x is cut into slabs and a launch has one block per (slab, tile) item, as in the
-//     exact sweep; the velocity read and the outputs are streamed past L2.
+//     exact sweep; the velocity read and the outputs follow its cache policy.
 // Stencils are evaluated in scaled form: 12 h D_i, and 144 h^2 for every second
 // difference (pure and mixed); the constant factors are folded into the weights.
 #pragma once
@@ -105,7 +105,7 @@ template <typename T> __device__ __forceinline__ T d2s(T m2, T m1, T c, T p1, T 
     return T(12) * fmaT(T(16), (p1 - c) + (m1 - c), -((p2 - c) + (m2 - c)));
 }
 
-template <typename T, int MODE, bool EXT> struct FormP {
+template <typename T, int MODE, bool EXT, int STREAM> struct FormP {
     using G = FpGeoOf<T>;
     using Smem = FormPSmem<T, G>;
     Smem& sm;
@@ -197,7 +197,7 @@ template <typename T, int MODE, bool EXT> struct FormP {
     {
         const unsigned base = (unsigned)clampi(x, 0, cm.n0 - 1) * cm.plane_b;
 #pragma unroll
-        for (int A = 0; A < 4; ++A) vnxt[A] = ldb_nt((gptr<const T>)cm.comp(cm.vel[0], A), base + off);
+        for (int A = 0; A < 4; ++A) vnxt[A] = ld_once<STREAM>((gptr<const T>)cm.comp(cm.vel[0], A), base + off);
     }
 
     // step s of the march: stage plane s, push D_x of its D_y phi and D_z phi, finish plane s-2
@@ -368,7 +368,7 @@ template <typename T, int MODE, bool EXT> struct FormP {
             if (cm.restore) {
 #pragma unroll
                 for (int A = 0; A < 4; ++A)
-                    stb_nt(cm.comp(cm.vel[0], A), base, cm.restore == RESTORE_ZERO ? T(0) : fmaT(-k.dtK, f[A], vcur[A]));
+                    st_once<STREAM>(cm.comp(cm.vel[0], A), base, cm.restore == RESTORE_ZERO ? T(0) : fmaT(-k.dtK, f[A], vcur[A]));
                 return;
             }
             T v[4], q[4], pn[4];
@@ -394,13 +394,13 @@ template <typename T, int MODE, bool EXT> struct FormP {
             }
 #pragma unroll
             for (int A = 0; A < 4; ++A) {
-                stb_nt(cm.comp(cm.pout[0], A), base, pn[A]);
-                stb_nt(cm.comp(cm.vel[0], A), base, v[A]);
+                st_once<STREAM>(cm.comp(cm.pout[0], A), base, pn[A]);
+                st_once<STREAM>(cm.comp(cm.vel[0], A), base, v[A]);
             }
         } else {
             if (cm.has_grad) {
 #pragma unroll
-                for (int A = 0; A < 4; ++A) stb_nt(cm.comp(cm.gout[0], A), base, (cm.projected ? -f[A] : g[A]) * k.invK);
+                for (int A = 0; A < 4; ++A) st_once<STREAM>(cm.comp(cm.gout[0], A), base, (cm.projected ? -f[A] : g[A]) * k.invK);
             }
         }
     }
@@ -439,7 +439,7 @@ template <typename T, int MODE, bool EXT> struct FormP {
 };
 
 // One block per (slab, tile) item, block i (after the XCD remap) taking items i, i + grid, ...
-template <typename T, int MODE, bool EXT>
+template <typename T, int MODE, bool EXT, int STREAM>
 __global__ __launch_bounds__(FpGeoOf<T>::THREADS) __attribute__((amdgpu_waves_per_eu(1, sizeof(T) == 8 ? 1 : 2)))
 void formp_kernel(SweepArgs a)
 {
@@ -510,7 +510,7 @@ void formp_kernel(SweepArgs a)
     const int tiles = a.tiles_y * a.tiles_z;
     const int x0 = a.olo[0], nx = a.ohi[0] - a.olo[0] + 1;
     const int items = tiles * ((nx + a.xchunk - 1) / a.xchunk);
-    FormP<T, MODE, EXT> fp(sm, k, cm, tid);
+    FormP<T, MODE, EXT, STREAM> fp(sm, k, cm, tid);
     for (int item = b; item < items; item += nb) {
         fp.setup(item_segment(item, tiles, a.tiles_z, x0, nx, a.xchunk), a.zstart);
         fp.march();

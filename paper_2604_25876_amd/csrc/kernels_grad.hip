@@ -1,0 +1,70 @@
+// The gradient / observables kernels and the printed-form kernels of both precisions, and the
+// choice between the precisions' kernels.
+#include "formp.hpp"
+#include "kernels.hpp"
+
+namespace skyr {
+
+template <typename T, class G> static const void* grad_of(int ext, int, int& threads)
+{
+    threads = G::THREADS;
+    if (ext == EXT_SEXTIC) return (const void*)sweep_kernel<T, G, MODE_GRAD, EXT_SEXTIC, STREAM_ALL>;
+    if (ext == EXT_POT) return (const void*)sweep_kernel<T, G, MODE_GRAD, EXT_POT, STREAM_ALL>;
+    return (const void*)sweep_kernel<T, G, MODE_GRAD, EXT_NONE, STREAM_ALL>;
+}
+
+const void* grad_kernel(skyr_precision prec, int variant, int ext, int& threads)
+{
+    const int stream = STREAM_ALL;
+    if (prec == SKYR_F64) {
+        int v = 0;
+#define SKYR_CASE(a, b, c, d, e, f) \
+    if (variant == v) return grad_of<double, Geo<a, b, c, d>>(ext, stream, threads); \
+    ++v;
+        SKYR_SHAPES_F64(SKYR_CASE)
+#undef SKYR_CASE
+    } else {
+        int v = 0;
+#define SKYR_CASE(a, b, c, d, e, f) \
+    if (variant == v) return grad_of<float, Geo<a, b, c, d>>(ext, stream, threads); \
+    ++v;
+        SKYR_SHAPES_F32(SKYR_CASE)
+#undef SKYR_CASE
+    }
+    threads = 0;
+    return nullptr;
+}
+
+const void* step_kernel(skyr_precision prec, int variant, int ext, int stream, int& threads)
+{
+    return prec == SKYR_F64 ? step_kernel_of<double>(variant, ext, stream, threads)
+                            : step_kernel_of<float>(variant, ext, stream, threads);
+}
+
+const void* batch_kernel(skyr_precision prec, int variant, int ext, int stream, int& threads)
+{
+    return prec == SKYR_F64 ? batch_kernel_of<double>(variant, ext, stream, threads)
+                            : batch_kernel_of<float>(variant, ext, stream, threads);
+}
+
+template <typename T, int MODE, bool EXT> static const void* printed_of(int stream)
+{
+    if constexpr (MODE == MODE_STEP) {
+        if (stream == STREAM_NONE) return (const void*)formp_kernel<T, MODE, EXT, STREAM_NONE>;
+        if (stream == STREAM_STORES) return (const void*)formp_kernel<T, MODE, EXT, STREAM_STORES>;
+    }
+    return (const void*)formp_kernel<T, MODE, EXT, STREAM_ALL>;
+}
+template <typename T> static const void* printed_of(int mode, bool ext, int stream)
+{
+    if (mode == MODE_STEP) return ext ? printed_of<T, MODE_STEP, true>(stream) : printed_of<T, MODE_STEP, false>(stream);
+    return ext ? printed_of<T, MODE_GRAD, true>(stream) : printed_of<T, MODE_GRAD, false>(stream);
+}
+
+const void* printed_kernel(skyr_precision prec, int mode, bool ext, int stream, int& threads)
+{
+    threads = prec == SKYR_F64 ? FpGeoF64::THREADS : FpGeoF32::THREADS;
+    return prec == SKYR_F64 ? printed_of<double>(mode, ext, stream) : printed_of<float>(mode, ext, stream);
+}
+
+}  // namespace skyr

@@ -20,6 +20,7 @@
 #include "sweep.hpp"
 #include "moments.hpp"
 #include "formp.hpp"
+#include "kernels.hpp"
 
 namespace skyr {
 
@@ -466,129 +467,46 @@ static int ext_level(const SweepArgs& a)
     return (a.m_y != 0.0 || a.m_z != 0.0 || a.m_w != 0.0 || a.gradient_flow != 0) ? EXT_POT : EXT_NONE;
 }
 
-template <typename T, class G, int MODE>
-static void launch_level(int ext, dim3 grid, dim3 block, const SweepArgs& args, hipStream_t s)
+// Cache policy of a step sweep over fields of `bytes` bytes in all (phi, phi_alt and vel of every
+// field that sweeps together).  Up to the last-level cache's 256 MB the next sweep finds them
+// there, and streaming them past it only costs: float 128^3 (101 MB) 44.4 us plain and 52.9
+// streamed, 151^3 (165 MB) 63.8 and 97.4, 176^3 (262 MB) 88 and 110; double 128^3 (201 MB) 67.6
+// and 76.5.  Above it streaming wins: double 144^3 (287 MB) 102.9 and 96.4, float 224^3 (539 MB)
+// 207 and 187, 256^3 (805 MB) 275 and 257.  Rows that are not whole 128-byte lines keep plain
+// velocity reads: a line is then read by two waves (double 151^3: 133.7 us against 151.1; whole
+// lines gain from streamed reads, 176^3 163 against 172).  Batches too: 49 against 53 ms for 48
+// steps of the 64-field mix.
+constexpr long long kLastLevelCache = 256LL << 20;
+static int stream_policy(long long bytes, bool whole_lines)
 {
-    if (ext == EXT_SEXTIC)
-        hipLaunchKernelGGL((sweep_kernel<T, G, MODE, EXT_SEXTIC>), grid, block, 0, s, args);
-    else if (ext == EXT_POT)
-        hipLaunchKernelGGL((sweep_kernel<T, G, MODE, EXT_POT>), grid, block, 0, s, args);
-    else
-        hipLaunchKernelGGL((sweep_kernel<T, G, MODE, EXT_NONE>), grid, block, 0, s, args);
+    if (bytes <= kLastLevelCache) return STREAM_NONE;
+    return whole_lines ? STREAM_ALL : STREAM_STORES;
 }
-
-template <typename T, class G>
-static hipError_t launch_shape(int mode, const Launch& L, const SweepArgs& args, hipStream_t s)
+// ... of one field whose arrays hold `array_sites` sites in rows of `row` elements
+static int field_policy(skyr_precision prec, long long array_sites, int row)
 {
-    const dim3 grid(L.blocks()), block(G::THREADS);
-    if (mode == MODE_STEP)
-        launch_level<T, G, MODE_STEP>(ext_level(args), grid, block, args, s);
-    else
-        launch_level<T, G, MODE_GRAD>(ext_level(args), grid, block, args, s);
-    return hipGetLastError();
+    const long long elem = prec == SKYR_F64 ? sizeof(double) : sizeof(float);
+    return stream_policy(3 * 4 * array_sites * elem, row * elem % 128 == 0);
 }
 
 static hipError_t sweep(skyr_precision prec, int mode, const Launch& L, const SweepArgs& args, hipStream_t s)
 {
-    int v = 0;
-    if (prec == SKYR_F64) {
-#define SKYR_CASE64(a, b, c, d, e, f)                                                                          \
-    if (L.variant == v) return launch_shape<double, Geo<a, b, c, d>>(mode, L, args, s);                      \
-    ++v;
-        SKYR_SHAPES_F64(SKYR_CASE64)
-#undef SKYR_CASE64
-    } else {
-#define SKYR_CASE32(a, b, c, d, e, f)                                                                          \
-    if (L.variant == v) return launch_shape<float, Geo<a, b, c, d>>(mode, L, args, s);                       \
-    ++v;
-        SKYR_SHAPES_F32(SKYR_CASE32)
-#undef SKYR_CASE32
-    }
-    return hipErrorInvalidValue;
-}
-
-// The step-sweep kernel of a tile shape at a kernel variant, and its block size (for
-// the nodes of a graph).
-template <typename T, class G> static const void* step_fn(int ext, int& threads)
-{
-    threads = G::THREADS;
-    if (ext == EXT_SEXTIC) return (const void*)sweep_kernel<T, G, MODE_STEP, EXT_SEXTIC>;
-    if (ext == EXT_POT) return (const void*)sweep_kernel<T, G, MODE_STEP, EXT_POT>;
-    return (const void*)sweep_kernel<T, G, MODE_STEP, EXT_NONE>;
-}
-
-static const void* step_kernel(skyr_precision prec, int variant, int ext, int& threads)
-{
-    int v = 0;
-    if (prec == SKYR_F64) {
-#define SKYR_S64(a, b, c, d, e, f)                                              \
-    if (variant == v) return step_fn<double, Geo<a, b, c, d>>(ext, threads); \
-    ++v;
-        SKYR_SHAPES_F64(SKYR_S64)
-#undef SKYR_S64
-    } else {
-#define SKYR_S32(a, b, c, d, e, f)                                             \
-    if (variant == v) return step_fn<float, Geo<a, b, c, d>>(ext, threads); \
-    ++v;
-        SKYR_SHAPES_F32(SKYR_S32)
-#undef SKYR_S32
-    }
-    threads = 0;
-    return nullptr;
-}
-
-template <typename T> static const void* printed_fn(int mode, bool ext)
-{
-    if (mode == MODE_STEP)
-        return ext ? (const void*)formp_kernel<T, MODE_STEP, true> : (const void*)formp_kernel<T, MODE_STEP, false>;
-    return ext ? (const void*)formp_kernel<T, MODE_GRAD, true> : (const void*)formp_kernel<T, MODE_GRAD, false>;
-}
-
-// the printed-form kernel of a precision and mode for arguments a, and its block size
-static const void* printed_kernel(skyr_precision prec, int mode, const SweepArgs& a, int& threads)
-{
-    const bool ext = ext_level(a) != EXT_NONE;
-    threads = prec == SKYR_F64 ? FpGeoF64::THREADS : FpGeoF32::THREADS;
-    return prec == SKYR_F64 ? printed_fn<double>(mode, ext) : printed_fn<float>(mode, ext);
+    int threads = 0;
+    const int ext = ext_level(args);
+    const void* fn = mode == MODE_GRAD ? grad_kernel(prec, L.variant, ext, threads)
+                                       : step_kernel(prec, L.variant, ext, args.stream, threads);
+    if (!fn) return hipErrorInvalidValue;
+    void* argv[1] = {const_cast<SweepArgs*>(&args)};
+    return hipLaunchKernel(fn, dim3(L.blocks()), dim3(threads), argv, 0, s);
 }
 
 // The printed-form sweep: one launch, arguments made by make_args with plan_printed's launch.
 static hipError_t sweep_printed(skyr_precision prec, int mode, const Launch& L, const SweepArgs& args, hipStream_t s)
 {
     int threads = 0;
-    const void* fn = printed_kernel(prec, mode, args, threads);
+    const void* fn = printed_kernel(prec, mode, ext_level(args) != EXT_NONE, args.stream, threads);
     void* argv[1] = {const_cast<SweepArgs*>(&args)};
     return hipLaunchKernel(fn, dim3(L.blocks()), dim3(threads), argv, 0, s);
-}
-
-// The batched-sweep kernel of one (precision, tile shape) group at a kernel variant, and
-// its block size.
-template <typename T, class G> static const void* batch_fn(int ext, int& threads)
-{
-    threads = G::THREADS;
-    if (ext == EXT_SEXTIC) return (const void*)batch_sweep_kernel<T, G, EXT_SEXTIC>;
-    if (ext == EXT_POT) return (const void*)batch_sweep_kernel<T, G, EXT_POT>;
-    return (const void*)batch_sweep_kernel<T, G, EXT_NONE>;
-}
-
-static const void* batch_kernel(skyr_precision prec, int variant, int ext, int& threads)
-{
-    int v = 0;
-    if (prec == SKYR_F64) {
-#define SKYR_B64(a, b, c, d, e, f)                                               \
-    if (variant == v) return batch_fn<double, Geo<a, b, c, d>>(ext, threads); \
-    ++v;
-        SKYR_SHAPES_F64(SKYR_B64)
-#undef SKYR_B64
-    } else {
-#define SKYR_B32(a, b, c, d, e, f)                                              \
-    if (variant == v) return batch_fn<float, Geo<a, b, c, d>>(ext, threads); \
-    ++v;
-        SKYR_SHAPES_F32(SKYR_B32)
-#undef SKYR_B32
-    }
-    threads = 0;
-    return nullptr;
 }
 
 static SweepArgs make_args(const skyr_lattice* lat, const Launch& L, const skyr_model* model, double dt)
@@ -1153,6 +1071,7 @@ static skyr_status anf_run(const skyr_lattice* lat, skyr_precision prec, const s
     if (pitch > 0) use_padded_rows(a, lat, lead, pitch);
     const long long array_sites = pitch > 0 ? (long long)lat->n[0] * lat->n[1] * pitch : sites(lat);
     a.gradient_flow = flow->mode == SKYR_GRADIENT_FLOW;
+    a.stream = field_policy(prec, array_sites, pitch > 0 ? pitch : lat->n[2]);
     a.phi0 = phi;
     a.phi1 = phi_alt;
     a.vel = vel;
@@ -1208,8 +1127,8 @@ static skyr_status anf_run(const skyr_lattice* lat, skyr_precision prec, const s
         if (graphs && group >= kFlowGraphSweeps) {
             const int reps = (int)(group / kFlowGraphSweeps);
             int threads = 0;
-            const void* fn = printed ? printed_kernel(prec, MODE_STEP, a, threads)
-                                     : step_kernel(prec, L.variant, ext_level(a), threads);
+            const void* fn = printed ? printed_kernel(prec, MODE_STEP, ext_level(a) != EXT_NONE, a.stream, threads)
+                                     : step_kernel(prec, L.variant, ext_level(a), a.stream, threads);
             const skyr_status rc = flow_graph_launch(fn, L.blocks(), threads, a, reps, s);
             if (rc != SKYR_OK) return rc;
             group = (int64_t)reps * kFlowGraphSweeps;
@@ -1587,6 +1506,7 @@ static skyr_status block_sweep_impl(const skyr_block* blk, skyr_precision prec, 
         a.phi1 = out;
         a.vel = vel;
         a.ctl = ctl;
+        a.stream = field_policy(prec, pitch > 0 ? (long long)g.P[0] * g.P[1] * pitch : g.sites(), pitch > 0 ? pitch : g.P[2]);
         hipLaunchKernelGGL(block_ctl_kernel, dim3(1), dim3(64), 0, s, ctl, redo ? 1 : 0,
                            (prec == SKYR_F32_BULK && renorm64) ? 1 : 0, L.blocks());
         SKYR_HIP(hipGetLastError());
@@ -1768,6 +1688,7 @@ skyr_status skyr_autotune(const skyr_lattice* lat, skyr_precision prec, const sk
         const Launch L = plan_with(lat, prec, cd.v, cd.xc);
         SweepArgs a = make_args(lat, L, model, flow->dt);
         a.gradient_flow = flow->mode == SKYR_GRADIENT_FLOW;
+        a.stream = field_policy(prec, sites(lat), lat->n[2]);
         a.phi0 = phi;
         a.phi1 = phi_alt;
         a.vel = vel;
@@ -1887,6 +1808,7 @@ struct skyr_batch {
     int map_cap[kChains] = {};
     int grid[kChains] = {};
     int ext[kChains] = {};  // the highest kernel variant a job of the chain needs
+    int stream_policy = 0;  // cache policy of the batch's sweeps, by the bytes of its fields
     bool dirty = true;       // the job tables need rebuilding
     bool params_stale = true;  // the graph's launch parameters predate the job tables
     hipGraphExec_t exec = nullptr;
@@ -2000,9 +1922,11 @@ static std::vector<int> chain_slots(const skyr_batch* b, const std::vector<int>&
 static skyr_status batch_rebuild(skyr_batch* b)
 {
     std::vector<int> count(b->max_jobs, 0), of_group[skyr_batch::kGroups];
+    long long bytes = 0;
     for (int j = 0; j < b->max_jobs; ++j) {
         const auto& J = b->jobs[j];
         if (!J.active) continue;
+        bytes += 3 * 4 * J.array_sites * (long long)elem_bytes(J.prec);
         count[j] = J.L.blocks();
         of_group[batch_group(J.prec, J.L.variant)].push_back(j);
     }
@@ -2026,6 +1950,7 @@ static skyr_status batch_rebuild(skyr_batch* b)
         b->grid[c] = (int)slots.size() / 2;
     }
     b->nchains = nc;
+    b->stream_policy = stream_policy(bytes, false);
     SKYR_HIP(hipMemcpy(b->d_count, count.data(), sizeof(int) * b->max_jobs, hipMemcpyHostToDevice));
     SKYR_HIP(hipMemcpy(b->d_args, b->args.data(), sizeof(SweepArgs) * b->max_jobs, hipMemcpyHostToDevice));
     b->dirty = false;
@@ -2041,7 +1966,7 @@ static hipKernelNodeParams chain_params(skyr_batch* b, int c, void** argv)
     const bool f64 = g < shape_count(SKYR_F64);
     int threads = 0;
     const void* fn = batch_kernel(f64 ? SKYR_F64 : SKYR_F32_BULK, f64 ? g : g - shape_count(SKYR_F64), b->ext[c],
-                                  threads);
+                                  b->stream_policy, threads);
     argv[0] = &b->d_args;
     argv[1] = &b->d_map[c];
     argv[2] = &b->d_count;

@@ -28,8 +28,9 @@
 //     double-buffered by plane parity, so one block barrier per plane suffices;
 //   * x is cut into slabs; a launch has one block per (slab, tile) item, so that the
 //     blocks of neighbouring tiles march through the same planes together and read the
-//     phi lines of their shared halo from L2 once; the velocity read and the outputs are
-//     streamed past L2 (non-temporal) so that they do not displace those lines.
+//     phi lines of their shared halo from L2 once; on fields larger than the last-level cache
+//     the velocity read and the outputs are streamed past the caches (non-temporal) so that
+//     they do not displace those lines.
 // Stencils are evaluated in the scaled form 8 (f[+1] - f[-1]) - (f[+2] - f[-2]) =
 // 12 h D f (and 16 (...) - (...) = 12 h^2 L f); the constant factors are folded into
 // the weights of the final sums.  Energy, charge and force sums are accumulated in
@@ -80,6 +81,16 @@ static_assert(sizeof(Ctl) <= 256, "control block must fit its 256-byte slot");
 
 enum : int { MODE_STEP = 0, MODE_GRAD = 1 };
 
+// Cache policy of a step sweep's accesses that are used once per sweep (the velocity read, the
+// outputs written); the host chooses it by the bytes of the fields (stream_policy in skyr.hip).
+// A template parameter of the kernels: as a branch around the accesses it split the plane's one
+// block of code and cost 10% (128^3 float) to 20% (256^3 double).
+enum : int {
+    STREAM_NONE = 0,    // plain accesses: the fields stay in the last-level cache between sweeps
+    STREAM_STORES = 1,  // non-temporal outputs
+    STREAM_ALL = 2      // non-temporal outputs and velocity reads
+};
+
 // The converging sweep over phi_k has already written v_k + dt F_k over v_k.  The sweep
 // after it recomputes F_k from phi_k (the same arithmetic, so the same F_k) and writes
 // v_k back: v - dt F_k, or exactly zero when v_k was zero (an arrest at step k, a redo
@@ -113,6 +124,7 @@ struct SweepArgs {
     double m, m_y, m_z, m_w;  // potential masses
     double c6;                // sextic (BPS-Skyrme) coefficient
     int gradient_flow;        // MODE_STEP: phi += dt F, no velocity
+    int stream;               // STREAM_*: chooses the step kernel (host only)
 };
 
 // stencil coefficients (Sec. 3)
@@ -154,20 +166,20 @@ template <typename T> __device__ __forceinline__ T ldb(gptr<const T> base, unsig
 {
     return *(gptr<const T>)((SKYR_GLOBAL const char*)base + off);
 }
-// Streamed accesses (the velocity read and the outputs written, used once per sweep):
-// non-temporal, so that they do not displace from L2 the phi lines that neighbouring
-// blocks read as their halo.
-template <typename T> __device__ __forceinline__ T ldb_nt(gptr<const T> base, unsigned off)
+// The accesses used once per sweep (the velocity read, the outputs written), by cache policy.
+template <int STREAM, typename T> __device__ __forceinline__ T ld_once(gptr<const T> base, unsigned off)
 {
-    return __builtin_nontemporal_load((gptr<const T>)((SKYR_GLOBAL const char*)base + off));
+    const gptr<const T> p = (gptr<const T>)((SKYR_GLOBAL const char*)base + off);
+    if constexpr (STREAM >= STREAM_ALL) return __builtin_nontemporal_load(p);
+    return *p;
 }
-template <typename T> __device__ __forceinline__ void stb_nt(gptr<T> base, unsigned off, T v)
+template <int STREAM, typename T> __device__ __forceinline__ void st_once(gptr<T> base, unsigned off, T v)
 {
-    __builtin_nontemporal_store(v, (gptr<T>)((SKYR_GLOBAL char*)base + off));
-}
-template <typename T> __device__ __forceinline__ void stb(gptr<T> base, unsigned off, T v)
-{
-    *(gptr<T>)((SKYR_GLOBAL char*)base + off) = v;
+    const gptr<T> p = (gptr<T>)((SKYR_GLOBAL char*)base + off);
+    if constexpr (STREAM >= STREAM_STORES)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
 }
 
 // a pointer that is the same in every lane, made visibly uniform (held in SGPRs)
@@ -420,7 +432,7 @@ template <typename T, bool FROM_TABLE> struct SweepCommon {
 
 // --------------------------------------------------------------- interior role
 // One output site per lane: row, col of the tile.
-template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interior {
+template <typename T, class G, int MODE, bool FROM_TABLE, int EXT, int STREAM> struct Interior {
     using Smem = SweepSmem<T, G>;
     Smem& sm;
     const SweepConst<T>& k;
@@ -561,7 +573,7 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
 #pragma unroll
             for (int A = 0; A < 4; ++A) {
                 vcur[A] = vnxt[A];
-                vnxt[A] = ldb_nt((gptr<const T>)cm.vel[A], vb + off);
+                vnxt[A] = ld_once<STREAM>((gptr<const T>)cm.vel[A], vb + off);
             }
         }
 #pragma unroll
@@ -717,7 +729,7 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
                 if (cm.restore) {
 #pragma unroll
                     for (int A = 0; A < 4; ++A)
-                        stb_nt(cm.vel[A], base, cm.restore == RESTORE_ZERO ? T(0) : fmaT(-k.dtK, f[A], vcur[A]));
+                        st_once<STREAM>(cm.vel[A], base, cm.restore == RESTORE_ZERO ? T(0) : fmaT(-k.dtK, f[A], vcur[A]));
                 } else {
                     T v[4], q[4], pn[4];
 #pragma unroll
@@ -743,14 +755,14 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
                     }
 #pragma unroll
                     for (int A = 0; A < 4; ++A) {
-                        stb_nt(cm.pout[A], base, pn[A]);
-                        stb_nt(cm.vel[A], base, v[A]);
+                        st_once<STREAM>(cm.pout[A], base, pn[A]);
+                        st_once<STREAM>(cm.vel[A], base, v[A]);
                     }
                 }
             } else {
                 if (cm.has_grad) {
 #pragma unroll
-                    for (int A = 0; A < 4; ++A) stb_nt(cm.gout[A], base, (cm.projected ? -f[A] : g[A]) * k.invK);
+                    for (int A = 0; A < 4; ++A) st_once<STREAM>(cm.gout[A], base, (cm.projected ? -f[A] : g[A]) * k.invK);
                 }
             }
         }
@@ -778,7 +790,7 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT> struct Interi
         if constexpr (MODE == MODE_STEP) {
             const unsigned vb = (unsigned)clampi(js - 2, 0, cm.n0 - 1) * cm.plane_b;
 #pragma unroll
-            for (int A = 0; A < 4; ++A) vnxt[A] = ldb_nt((gptr<const T>)cm.vel[A], vb + off);
+            for (int A = 0; A < 4; ++A) vnxt[A] = ld_once<STREAM>((gptr<const T>)cm.vel[A], vb + off);
         }
         sm.phi[0].st(pidx + PO, ring[2]);
         __syncthreads();
@@ -1126,7 +1138,7 @@ __device__ __forceinline__ void finish_step(const double* part, int nb, Ctl* ctl
 // One block's share of one field: logical block b of nb blocks, which takes the items b,
 // b + nb, ... of the field's work.  Used by the single-field and the batched kernels
 // (FROM_TABLE: the arguments were read from the batch's job table).
-template <typename T, class G, int MODE, bool FROM_TABLE = false, int EXT = EXT_NONE>
+template <typename T, class G, int MODE, bool FROM_TABLE, int EXT, int STREAM>
 __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, SweepSmem<T, G>& sm)
 {
     SweepCommon<T, FROM_TABLE> cm;
@@ -1198,7 +1210,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, S
 
     double vals[7] = {0, 0, 0, 0, 0, 0, 0};
     if (wave < G::NWI) {
-        Interior<T, G, MODE, FROM_TABLE, EXT> it(sm, k, cm, tid);
+        Interior<T, G, MODE, FROM_TABLE, EXT, STREAM> it(sm, k, cm, tid);
         for (int item = b; item < items; item += nb) {
             it.setup(item_segment(item, tiles, a.tiles_z, x0, nx, a.xchunk), a.zstart);
             it.march();
@@ -1254,12 +1266,12 @@ __device__ __forceinline__ int xcd_logical_block(int i, int n)
     return xcd * q8 + min(xcd, r8) + i / 8;
 }
 
-template <typename T, class G, int MODE, int EXT>
+template <typename T, class G, int MODE, int EXT, int STREAM>
 __global__ __launch_bounds__(G::THREADS) void sweep_kernel(SweepArgs a)
 {
     __shared__ SweepSmem<T, G> smem;
     const int nb = gridDim.x;
-    sweep_block<T, G, MODE, false, EXT>(a, xcd_logical_block(blockIdx.x, nb), nb, smem);
+    sweep_block<T, G, MODE, false, EXT, STREAM>(a, xcd_logical_block(blockIdx.x, nb), nb, smem);
 }
 
 // Many fields in one launch: launch block p sweeps block slot[p].y of field slot[p].x
@@ -1267,7 +1279,7 @@ __global__ __launch_bounds__(G::THREADS) void sweep_kernel(SweepArgs a)
 // slots out for the round-robin dispatch of blocks over the XCDs (block p runs on XCD
 // p mod 8); every field's blocks and partial sums are exactly those of a launch of that
 // field alone.
-template <typename T, class G, int EXT>
+template <typename T, class G, int EXT, int STREAM>
 __global__ __launch_bounds__(G::THREADS) void batch_sweep_kernel(const SweepArgs* __restrict__ jobs,
                                                                  const int2* __restrict__ slot,
                                                                  const int* __restrict__ blocks_of_job)
@@ -1276,7 +1288,7 @@ __global__ __launch_bounds__(G::THREADS) void batch_sweep_kernel(const SweepArgs
     const int2 e = slot[blockIdx.x];
     if (e.x < 0) return;
     const SweepArgs a = jobs[e.x];
-    sweep_block<T, G, MODE_STEP, true, EXT>(a, e.y, blocks_of_job[e.x], smem);
+    sweep_block<T, G, MODE_STEP, true, EXT, STREAM>(a, e.y, blocks_of_job[e.x], smem);
 }
 
 }  // namespace skyr
