@@ -517,7 +517,11 @@ SKYR_API skyr_status skyr_batch_destroy(skyr_batch* b);
  * Default for a field flowing alone (a lattice never set or tuned): the shape
  * and even split of x into 1..8 slabs of least estimated time, that is the
  * rounds of the device its blocks take times the padded work of one block,
- * each shape priced by a factor measured at 256^3.  Fields in batches have a
+ * each shape priced by a factor measured at 256^3.  A sweep on the default tile may
+ * launch with another shape and shorter slabs where that is faster (a small lattice
+ * on more of the device): field values do not depend on either, only the order of
+ * the sums does.  A tile set to the default choice is the default; any other is used
+ * as it was set.  Fields in batches have a
  * tile setting of their own (skyr_set_batch_tile, skyr_batch_autotune) whose
  * default is the precision's first shape (variant 0: the fields of one
  * precision then share one launch per sweep slot) with x split evenly into the

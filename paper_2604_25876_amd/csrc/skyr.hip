@@ -170,19 +170,84 @@ static void default_tile(const skyr_lattice* lat, skyr_precision prec, int& v_ou
         }
 }
 
+// Launch of a lattice on its default tile.  The tile itself (variant, planes per slab of at least
+// kMinChunk) stays what skyr_get_tile reports; the launch may take another shape and shorter
+// slabs, since field values do not depend on either.  A block marches xc + 4 planes and pays for
+// about two more (its first loads, its sums); a launch of r rounds of the chip takes r (xc + 6)
+// times the time of a step of its shape, 15% more when r > 1.  With the step times below this picks
+// within 1.2% of the fastest of all (shape, slab length) pairs, measured on cubes of 40 .. 256
+// sites in both precisions: one round with as many slabs as it holds, where the lattice is small
+// enough.  40^3: 2-plane slabs, 108-162 blocks, 19-21 us a sweep against 42-43.5 with the default
+// tile's 18 blocks; 96^3: 31 / 39 us (float / double) against 44 / 47; 128^3 float 41 against 44;
+// 256^3 double on 8 x 32 tiles 451 against 478.
+constexpr double kStepF64[] = {1.6, 1.52, 2.2};  // microseconds a step, one block per CU
+constexpr double kStepF32[] = {1.5, 1.3, 2.0};
+constexpr double kStepF32Pair = 2.2;  // the second float shape with two blocks on a CU
+// no launch has more blocks than every workspace (and the fixed scratch) has records for
+constexpr int kMaxBlocks = 4084;
+
+static double launch_cost(skyr_precision prec, int v, int xc, long long blocks)
+{
+    const Shape& sh = shape_of(prec, v);
+    const bool pair = sh.per_cu > 1 && blocks > kCUs;
+    const long long per_round = (long long)kCUs * (pair ? sh.per_cu : 1);
+    const long long rounds = (blocks + per_round - 1) / per_round;
+    const double step = prec == SKYR_F64 ? kStepF64[v] : pair ? kStepF32Pair : kStepF32[v];
+    return (double)rounds * (rounds > 1 ? kMultiRoundCost : 1.0) * (xc + 6) * step;
+}
+
+// the even splits of nx planes into 1, 2, ... slabs: next_split gives the slab length of the next
+// one (the number of slabs grows), 0 when the planes do not divide further
+static int next_split(int nx, int xc)
+{
+    if (xc <= 1) return 0;
+    const int slabs = (nx + xc - 1) / xc;
+    return std::min(xc - 1, (nx + slabs) / (slabs + 1));
+}
+
+static Launch default_launch(const skyr_lattice* lat, skyr_precision prec, int v0, int xc0)
+{
+    Launch best = plan_with(lat, prec, v0, xc0);
+    double least = best.blocks() <= kMaxBlocks ? launch_cost(prec, v0, xc0, best.blocks()) : INFINITY;
+    const int nx = lat->n[0] - 4;
+    for (int v = 0; v < shape_count(prec); ++v)
+        for (int xc = nx; xc > 0; xc = next_split(nx, xc)) {
+            const Launch L = plan_with(lat, prec, v, xc);
+            if (L.blocks() > kMaxBlocks) break;
+            const double c = launch_cost(prec, v, xc, L.blocks());
+            if (c < least * (1.0 - 1e-9)) {
+                least = c;
+                best = L;
+            }
+        }
+    return best;
+}
+
+// the launch of a lattice: its own tile where one was set or tuned, else the default's
 static Launch plan(const skyr_lattice* lat, skyr_precision prec)
 {
     int v = 0, xc = 0;
+    default_tile(lat, prec, v, xc);
     {
         std::lock_guard<std::mutex> g(g_tile_mu);
         auto it = g_tiles.find(TileKey{lat->n[0], lat->n[1], lat->n[2], (int)prec});
-        if (it != g_tiles.end()) {
-            v = it->second.first;
-            xc = it->second.second;
-        }
+        if (it != g_tiles.end() && it->second != std::make_pair(v, xc))
+            return plan_with(lat, prec, it->second.first, it->second.second);
     }
-    if (xc == 0) default_tile(lat, prec, v, xc);
-    return plan_with(lat, prec, v, xc);
+    return default_launch(lat, prec, v, xc);
+}
+
+// the tile in force, as the getters report it
+static std::pair<int, int> tile_in_force(const skyr_lattice* lat, skyr_precision prec)
+{
+    {
+        std::lock_guard<std::mutex> g(g_tile_mu);
+        auto it = g_tiles.find(TileKey{lat->n[0], lat->n[1], lat->n[2], (int)prec});
+        if (it != g_tiles.end()) return it->second;
+    }
+    int v = 0, xc = 0;
+    default_tile(lat, prec, v, xc);
+    return {v, xc};
 }
 
 // Tile shape and slab length of a field in a batch on a lattice that no one has set or
@@ -219,7 +284,7 @@ static Launch plan_batch(const skyr_lattice* lat, skyr_precision prec)
 }
 
 // The printed-form sweep: its fixed tile shape, one block per (slab, tile) item, and the
-// slab length whose items cost least in rounds of the chip (as for the exact sweep).
+// slab length whose items cost least in rounds of the chip (as default_launch counts them).
 static Launch plan_printed(const skyr_lattice* lat, skyr_precision prec)
 {
     const int oy = prec == SKYR_F64 ? FpGeoF64::OY : FpGeoF32::OY;
@@ -229,13 +294,13 @@ static Launch plan_printed(const skyr_lattice* lat, skyr_precision prec)
     L.shape = Shape{oy * oz / 64, 0, 0, oz, 1, 1.0};
     tile_grid(lat, L.shape, L.tiles_y, L.tiles_z, L.zstart);
     const int nx = lat->n[0] - 4, tiles = L.tiles_y * L.tiles_z;
-    const int most = std::max(1, std::min(kMaxSlabs, nx / kMinChunk));
     double best = INFINITY;
-    for (int sl = 1; sl <= most; ++sl) {
-        const int xc = std::max(1, (nx + sl - 1) / sl);
+    L.xchunk = nx;
+    for (int xc = nx; xc > 0; xc = next_split(nx, xc)) {
         const long long items = (long long)tiles * ((nx + xc - 1) / xc);
+        if (items > kMaxBlocks && xc < nx) break;
         const long long rounds = (items + kCUs - 1) / kCUs;
-        const double c = (double)rounds * (rounds > 1 ? kMultiRoundCost : 1.0) * (xc + 4);
+        const double c = (double)rounds * (rounds > 1 ? kMultiRoundCost : 1.0) * (xc + 6);
         if (c < best * (1.0 - 1e-9)) {
             best = c;
             L.xchunk = xc;
@@ -1605,9 +1670,9 @@ skyr_status skyr_get_tile(const skyr_lattice* lat, skyr_precision prec, int32_t*
 {
     skyr_status st = check_lattice(lat, prec);
     if (st != SKYR_OK) return st;
-    const Launch L = plan(lat, prec);
-    if (variant) *variant = L.variant;
-    if (xchunk) *xchunk = L.xchunk;
+    const std::pair<int, int> t = tile_in_force(lat, prec);
+    if (variant) *variant = t.first;
+    if (xchunk) *xchunk = t.second;
     return SKYR_OK;
 }
 
@@ -1684,8 +1749,11 @@ skyr_status skyr_autotune(const skyr_lattice* lat, skyr_precision prec, const sk
             cands.push_back({v, xc, INFINITY, {}});
         }
     }
+    int dv = 0, dx = 0;
+    default_tile(lat, prec, dv, dx);
     auto time_one = [&](Cand& cd, int warm, bool round) -> hipError_t {
-        const Launch L = plan_with(lat, prec, cd.v, cd.xc);
+        // the default choice as it would run
+        const Launch L = cd.v == dv && cd.xc == dx ? default_launch(lat, prec, dv, dx) : plan_with(lat, prec, cd.v, cd.xc);
         SweepArgs a = make_args(lat, L, model, flow->dt);
         a.gradient_flow = flow->mode == SKYR_GRADIENT_FLOW;
         a.stream = field_policy(prec, sites(lat), lat->n[2]);
@@ -1722,8 +1790,6 @@ skyr_status skyr_autotune(const skyr_lattice* lat, skyr_precision prec, const sk
     for (size_t i = 0; i < cands.size() && e == hipSuccess; ++i) e = time_one(cands[i], 1, false);
     // the closest candidates and the default choice are timed again in interleaved rounds;
     // a finalist's time is the median of its rounds (a single lucky round does not decide)
-    int dv = 0, dx = 0;
-    default_tile(lat, prec, dv, dx);
     size_t di = cands.size();
     for (size_t i = 0; i < cands.size(); ++i)
         if (cands[i].v == dv && cands[i].xc == dx) di = i;
