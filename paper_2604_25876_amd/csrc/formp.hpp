@@ -517,27 +517,8 @@ void formp_kernel(SweepArgs a)
         __syncthreads();  // the next item's first planes reuse the buffers
     }
 
-    // block reduction of the partial sums (fixed order), the layout of the exact sweep
-    double vals[7] = {fp.pe2, fp.pe4, fp.pe0, fp.pb_sum * k.dinv12h3, (double)fp.pf2 * k.dinvK2, fp.pp * k.dinvK, 0.0};
-    const int lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) {
-        double v = vals[i];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const double w = __shfl_xor(v, o);
-            v = (i == P_F2) ? fmax(v, w) : v + w;
-        }
-        if (lane == 0) sm.red[wave][i] = v;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        double sum[7] = {0, 0, 0, 0, 0, 0, 0};
-        for (int w = 0; w < G::NW; ++w)
-            for (int i = 0; i < 7; ++i) sum[i] = (i == P_F2) ? fmax(sum[i], sm.red[w][i]) : sum[i] + sm.red[w][i];
-        double* o = a.partials + (size_t)b * NPART;
-        for (int i = 0; i < 7; ++i) __hip_atomic_store(o + i, sum[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    block_sums<G::NW, MODE == MODE_STEP>(fp.pe2, (double)fp.pf2 * k.dinvK2, fp.pp * k.dinvK, fp.pe4, fp.pe0,
+                                         fp.pb_sum * k.dinv12h3, 0.0, a.partials + (size_t)b * NPART, sm);
     if constexpr (MODE == MODE_STEP)
         finish_step<G::THREADS, G::NW>(a.partials, nb, a.ctl, cm.restore != RESTORE_NONE, sm);
 }

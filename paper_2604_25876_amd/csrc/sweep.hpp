@@ -1024,18 +1024,19 @@ template <typename T, class G, bool FROM_TABLE, int EXT> struct Halo {
     }
 };
 
-// The flow's decision after the sweep over phi_k (Sec. 3), from the sums of that sweep
-// (s: the reduced partial-sum slots): arrest when E_k > E_{k-1} (energy rule) or when the
-// power h^3 sum F_k . v_k < 0 (power rule), re-running the sweep with v_k = 0; stop when
-// max|F_k| < tol; otherwise accept the update (swap the field buffers).  One thread.
-__device__ inline void flow_decide(const double* s, Ctl* ctl)
+// The flow's decision after the sweep over phi_k (Sec. 3), from the sums of that sweep (the
+// energy density, the largest |F|^2, the power): arrest when E_k > E_{k-1} (energy rule) or when
+// the power h^3 sum F_k . v_k < 0 (power rule), re-running the sweep with v_k = 0; stop when
+// max|F_k| < tol; otherwise accept the update (swap the field buffers).  c: the control block as
+// read before the sums were complete; the fields that change are written to ctl.  One thread.
+__device__ inline void flow_decide(double sum_e, double max_f2, double sum_pow, const Ctl& c, Ctl* ctl)
 {
-    // the flow sweep sums the whole energy density in slot P_E2 (slots P_E4, P_E0, P_E6 are zero)
-    const double E = ctl->h3 * s[P_E2];
-    const double r = sqrt(s[P_F2]);
-    ctl->sweeps += 1;
+    const double E = c.h3 * sum_e;
+    const double P = c.h3 * sum_pow;
+    const double r = sqrt(max_f2);
+    ctl->sweeps = c.sweeps + 1;
     ctl->E = E;
-    ctl->P = ctl->h3 * s[P_POW];
+    ctl->P = P;
     ctl->max_force = r;
     if (!isfinite(E) || !isfinite(r)) {
         ctl->done = 1;
@@ -1043,34 +1044,66 @@ __device__ inline void flow_decide(const double* s, Ctl* ctl)
         return;
     }
     bool arrest = false;
-    if (!ctl->redo && ((ctl->flow_mode == SKYR_ARREST_POWER && ctl->P < 0.0) ||
-                       (ctl->flow_mode == SKYR_ARREST_ENERGY && E > ctl->E_prev))) {
+    if (!c.redo && ((c.flow_mode == SKYR_ARREST_POWER && P < 0.0) ||
+                    (c.flow_mode == SKYR_ARREST_ENERGY && E > c.E_prev))) {
         arrest = true;
-        ctl->arrests += 1;
+        ctl->arrests = c.arrests + 1;
     }
-    if (r < ctl->tol) {
+    if (r < c.tol) {
         ctl->done = 1;
         ctl->status = 1;
         // the sweep wrote v_k + dt F_k over v_k; the next one puts v_k back (zero if v_k was
         // reset by an arrest at this step or was zero on this redo sweep)
-        const bool v_zero = ctl->redo || arrest || ctl->flow_mode == SKYR_GRADIENT_FLOW;
+        const bool v_zero = c.redo || arrest || c.flow_mode == SKYR_GRADIENT_FLOW;
         ctl->restore = v_zero ? RESTORE_ZERO : RESTORE_UNKICK;
         ctl->redo = 0;
         return;
     }
     if (arrest) {
         ctl->redo = 1;
-        ctl->redo_sweeps += 1;
+        ctl->redo_sweeps = c.redo_sweeps + 1;
         return;
     }
-    ctl->cur ^= 1;
+    ctl->cur = c.cur ^ 1;
     ctl->redo = 0;
     ctl->E_prev = E;
-    ctl->steps += 1;
-    if (ctl->steps >= ctl->target) {
+    ctl->steps = c.steps + 1;
+    if (c.steps + 1 >= c.target) {
         ctl->done = 1;
         ctl->status = 2;
     }
+}
+
+// v of another lane, by cross-lane moves of the vector unit (the shuffles of a butterfly went
+// through LDS, six dependent round trips a sum)
+template <int CTRL> __device__ __forceinline__ double dpp_f64(double v)
+{
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)u, CTRL, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+// The sum (maximum) of v over the wave, in every lane, in a fixed order: lanes 1 and 2 away, then
+// (the sums of all lanes of a quad being equal) the mirrored lanes of 8 and 16, then the lanes 16
+// and 32 away: a swap of two copies' halves leaves one half's sum in one copy and the other's in
+// the other.
+template <bool MAX> __device__ __forceinline__ double wave_total(double v)
+{
+    const auto add = [](double a, double b) { return MAX ? fmax(a, b) : a + b; };
+    v = add(v, dpp_f64<0xb1>(v));   // quad lanes 1, 0, 3, 2
+    v = add(v, dpp_f64<0x4e>(v));   // quad lanes 2, 3, 0, 1
+    v = add(v, dpp_f64<0x141>(v));  // mirrored in 8 lanes
+    v = add(v, dpp_f64<0x140>(v));  // mirrored in 16 lanes
+    const auto halves = [&](auto swap) {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        const auto lo = swap((unsigned)u), hi = swap((unsigned)(u >> 32));
+        const double x = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
+        const double y = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+        return add(x, y);
+    };
+    v = halves([](unsigned u) { return __builtin_amdgcn_permlane16_swap(u, u, false, false); });
+    v = halves([](unsigned u) { return __builtin_amdgcn_permlane32_swap(u, u, false, false); });
+    return v;
 }
 
 // End of a step sweep: every block has published its partial sums; the block that
@@ -1078,17 +1111,22 @@ __device__ inline void flow_decide(const double* s, Ctl* ctl)
 // fixed order (thread t takes blocks t, t + THREADS, ..., then a fixed butterfly per wave
 // and the waves in order) and takes the flow's decision.  A restore sweep only clears the
 // restore flag; a sweep on a held control block only resets the ticket.
-// The partial sums are agent-scope atomic stores, complete (s_waitcnt) before the block's
-// ticket, and the last block reads them with agent-scope atomic loads: they are coherent
+// The partial sums are agent-scope atomic stores of wave 0, complete (s_waitcnt) before the
+// block's ticket, and the last block reads them with agent-scope atomic loads: they are coherent
 // across the XCDs' L2 caches without a device-wide fence, which would write back and
 // invalidate the whole L2 of the block's XCD while its neighbours still read halo lines.
-// The fields of the control block other than the ticket change only between launches.
+// The fields of the control block other than the ticket change only between launches: thread 0
+// reads those of the decision while the partial sums are on their way.
+// Only the three sums that the decision needs are reduced, on the vector unit, and nothing waits
+// twice: 40^3 double (six march steps a block) 19.2 -> 17.9 us a sweep, 256^3 float 2% faster.
 // Smem: shared memory with `int last` and `double red[NW][NPART]`; THREADS threads in NW waves.
 template <int THREADS, int NW, class Smem>
 __device__ __forceinline__ void finish_step(const double* part, int nb, Ctl* ctl, bool restore, Smem& sm)
 {
     const int tid = threadIdx.x;
+    Ctl c{};
     if (tid == 0) {
+        c = *ctl;
         __builtin_amdgcn_s_waitcnt(0);  // this block's partial sums before its ticket
         sm.last = __hip_atomic_fetch_add(&ctl->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nb - 1;
     }
@@ -1101,37 +1139,81 @@ __device__ __forceinline__ void finish_step(const double* part, int nb, Ctl* ctl
         }
         return;
     }
-    double v[NRED];
-#pragma unroll
-    for (int i = 0; i < NRED; ++i) v[i] = 0.0;
+    // the flow sweep sums the whole energy density in slot P_E2 (slots P_E4, P_E0, P_E6 are zero)
+    double e = 0.0, f2 = 0.0, pw = 0.0;
     for (int b = tid; b < nb; b += THREADS) {
         const double* p = part + (size_t)b * NPART;
-#pragma unroll
-        for (int i = 0; i < NRED; ++i) {
-            const double x = __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            v[i] = (i == P_F2) ? fmax(v[i], x) : v[i] + x;
-        }
+        const double x0 = __hip_atomic_load(p + P_E2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const double x1 = __hip_atomic_load(p + P_F2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const double x2 = __hip_atomic_load(p + P_POW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        e += x0;
+        f2 = fmax(f2, x1);
+        pw += x2;
     }
+    e = wave_total<false>(e);
+    f2 = wave_total<true>(f2);
+    pw = wave_total<false>(pw);
     const int lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-    for (int i = 0; i < NRED; ++i) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const double w = __shfl_xor(v[i], o);
-            v[i] = (i == P_F2) ? fmax(v[i], w) : v[i] + w;
-        }
-        if (lane == 0) sm.red[wave][i] = v[i];
+    if (lane == 0) {
+        sm.red[wave][0] = e;
+        sm.red[wave][1] = f2;
+        sm.red[wave][2] = pw;
     }
     __syncthreads();
     if (tid == 0) {
-        double sum[NRED];
+        e = f2 = pw = 0.0;
 #pragma unroll
-        for (int i = 0; i < NRED; ++i) sum[i] = 0.0;
-        for (int w = 0; w < NW; ++w)
-#pragma unroll
-            for (int i = 0; i < NRED; ++i) sum[i] = (i == P_F2) ? fmax(sum[i], sm.red[w][i]) : sum[i] + sm.red[w][i];
-        flow_decide(sum, ctl);
+        for (int w = 0; w < NW; ++w) {
+            e += sm.red[w][0];
+            f2 = fmax(f2, sm.red[w][1]);
+            pw += sm.red[w][2];
+        }
+        flow_decide(e, f2, pw, c, ctl);
         __hip_atomic_store(&ctl->ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// A block's sums over its threads, in a fixed order (a butterfly per wave, then waves 0 .. NWS-1),
+// published as the block's record.  e2: in a step sweep the whole energy density (the parts and the
+// charge are then not summed).  Lane i of wave 0 publishes slot i.
+template <int NWS, bool STEP, class Smem>
+__device__ __forceinline__ void block_sums(double e2, double f2, double pw, double e4, double e0, double b, double e6,
+                                           double* record, Smem& sm)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (wave < NWS) {
+        e2 = wave_total<false>(e2);
+        f2 = wave_total<true>(f2);
+        if constexpr (STEP) {
+            pw = wave_total<false>(pw);
+        } else {
+            e4 = wave_total<false>(e4);
+            e0 = wave_total<false>(e0);
+            b = wave_total<false>(b);
+            e6 = wave_total<false>(e6);
+        }
+        if (lane == 0) {
+            double* r = sm.red[wave];
+            r[P_E2] = e2;
+            r[P_E4] = STEP ? 0.0 : e4;
+            r[P_E0] = STEP ? 0.0 : e0;
+            r[P_B] = STEP ? 0.0 : b;
+            r[P_F2] = f2;
+            r[P_POW] = STEP ? pw : 0.0;
+            r[P_E6] = STEP ? 0.0 : e6;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < NRED) {
+        const int i = threadIdx.x;
+        double sum = 0.0, most = 0.0;
+#pragma unroll
+        for (int w = 0; w < NWS; ++w) {
+            const double v = sm.red[w][i];
+            sum += v;
+            most = fmax(most, v);
+        }
+        __hip_atomic_store(record + i, i == P_F2 ? most : sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -1208,20 +1290,20 @@ __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, S
     const int x0 = a.olo[0], nx = a.ohi[0] - a.olo[0] + 1;
     const int items = tiles * ((nx + a.xchunk - 1) / a.xchunk);
 
-    double vals[7] = {0, 0, 0, 0, 0, 0, 0};
+    double e2 = 0.0, e4 = 0.0, e0 = 0.0, e6 = 0.0, bsum = 0.0, f2 = 0.0, pw = 0.0;
     if (wave < G::NWI) {
         Interior<T, G, MODE, FROM_TABLE, EXT, STREAM> it(sm, k, cm, tid);
         for (int item = b; item < items; item += nb) {
             it.setup(item_segment(item, tiles, a.tiles_z, x0, nx, a.xchunk), a.zstart);
             it.march();
         }
-        vals[0] = it.pe2;
-        vals[1] = it.pe4;
-        vals[2] = it.pe0;
-        vals[3] = it.pb_sum * k.dinv12h3;
-        vals[4] = (double)it.pf2 * k.dinvK2;
-        vals[5] = it.pp * k.dinvK;
-        vals[6] = it.pe6;
+        e2 = it.pe2;
+        e4 = it.pe4;
+        e0 = it.pe0;
+        bsum = it.pb_sum * k.dinv12h3;
+        f2 = (double)it.pf2 * k.dinvK2;
+        pw = it.pp * k.dinvK;
+        e6 = it.pe6;
     } else {
         Halo<T, G, FROM_TABLE, EXT> hl(sm, k, cm, tid - G::NWI * 64);
         for (int item = b; item < items; item += nb) {
@@ -1229,30 +1311,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, S
             hl.march();
         }
     }
-
-    // block reduction of the partial sums (fixed order)
-#pragma unroll
-    for (int i = 0; i < 7; ++i) {
-        double v = vals[i];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const double w = __shfl_xor(v, o);
-            v = (i == P_F2) ? fmax(v, w) : v + w;
-        }
-        vals[i] = v;
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int i = 0; i < 7; ++i) sm.red[wave][i] = vals[i];
-    }
-    __syncthreads();
-    if (tid == 0) {
-        double sum[7] = {0, 0, 0, 0, 0, 0, 0};
-        for (int wv = 0; wv < G::NWI; ++wv)
-            for (int i = 0; i < 7; ++i) sum[i] = (i == P_F2) ? fmax(sum[i], sm.red[wv][i]) : sum[i] + sm.red[wv][i];
-        double* o = a.partials + (size_t)b * NPART;
-        for (int i = 0; i < 7; ++i) __hip_atomic_store(o + i, sum[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    block_sums<G::NWI, MODE == MODE_STEP>(e2, f2, pw, e4, e0, bsum, e6, a.partials + (size_t)b * NPART, sm);
     if constexpr (MODE == MODE_STEP) finish_step<G::THREADS, G::NW>(a.partials, nb, a.ctl, cm.restore != RESTORE_NONE, sm);
 }
 
