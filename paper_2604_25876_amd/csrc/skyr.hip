@@ -1384,12 +1384,52 @@ __device__ __forceinline__ long long shell_rank(int x, int y, int z, int P1, int
     return r + 4LL * P2 + (long long)(y - 4) * (P2 - e2) + (z < 4 ? z : z - e2);
 }
 
-// The shell of a padded block field.  Pass 0: shell sites inside the lattice from the
-// shell buffer.  Pass 1 (after pass 0): shell sites outside the lattice from the nearest
-// lattice site, which pass 0 or the own box has filled.
+// padded site of shell rank r: the inverse of shell_rank
+__device__ __forceinline__ void shell_site(unsigned r, const BlockGeo& g, int& x, int& y, int& z)
+{
+    const unsigned P1 = g.P[1], P2 = g.P[2], e0 = g.e[0], e1 = g.e[1], e2 = g.e[2];
+    const unsigned plane = P1 * P2, ring = plane - e1 * e2;
+    // four whole planes, the rings around the own rows of e0 planes, four whole planes
+    unsigned t = r, first = 0;  // rank within the run of whole rows that the site belongs to, and its first row
+    if (r < 4 * plane) {
+        x = (int)(r / plane);
+        t = r - (unsigned)x * plane;
+    } else if (r - 4 * plane >= e0 * ring) {
+        r -= 4 * plane + e0 * ring;
+        x = (int)(r / plane);
+        t = r - (unsigned)x * plane;
+        x += 4 + (int)e0;
+    } else {
+        r -= 4 * plane;
+        x = (int)(r / ring);
+        t = r - (unsigned)x * ring;
+        x += 4;
+        if (t >= 4 * P2) {
+            t -= 4 * P2;
+            if (t < 8 * e1) {  // four columns on either side of an own row
+                const unsigned c = t % 8;
+                y = 4 + (int)(t / 8);
+                z = (int)(c < 4 ? c : c + e2);
+                return;
+            }
+            t -= 8 * e1;
+            first = 4 + e1;
+        }
+    }
+    y = (int)(t / P2);
+    z = (int)(t - (unsigned)y * P2);
+    y += (int)first;
+}
+
+// The shell of a padded block field, one thread per shell site: sites inside the lattice from
+// the shell buffer, the others from the nearest lattice site (one of the block's own or of the
+// shell buffer).  The first thread writes the step sweep's control block (ctl null: none): no
+// decision taken (the caller's), state as given.  Only the shell is visited: 418,000 of the 2.5
+// million sites of a 128^3 block's box; two passes over the whole box and a launch for the control
+// block took 36 us, more than half of that block's float sweep.
 template <typename T>
-__global__ void block_shell_kernel(T* __restrict__ phi, const T* __restrict__ shell, BlockGeo g, int pass, int lead,
-                                   int pitch)
+__global__ void block_shell_kernel(T* __restrict__ phi, const T* __restrict__ shell, BlockGeo g, int lead, int pitch,
+                                   Ctl* __restrict__ ctl, int redo, int renorm64, int nblocks)
 {
     const long long N = g.sites(), S = g.shell();
     const int P1 = g.P[1], P2 = g.P[2];
@@ -1399,52 +1439,43 @@ __global__ void block_shell_kernel(T* __restrict__ phi, const T* __restrict__ sh
         return pitch > 0 ? ((long long)((long long)x * P1 + y) * 4 + A) * pitch + lead + z
                          : (long long)A * N + ((long long)x * P1 + y) * P2 + z;
     };
-    for (long long s = (long long)blockIdx.x * blockDim.x + threadIdx.x; s < N; s += (long long)gridDim.x * blockDim.x) {
-        const int z = (int)(s % P2), y = (int)((s / P2) % P1), x = (int)(s / ((long long)P1 * P2));
-        const int p[3] = {x, y, z};
-        bool own = true, inside = true;
-        int q[3];
+    if (ctl && blockIdx.x == 0 && threadIdx.x == 0) {
+        Ctl c{};
+        c.redo = redo;
+        c.renorm64_every = renorm64 ? 1 : 0;
+        c.nblocks = nblocks;
+        c.hold = 1;
+        c.target = INT64_MAX;
+        c.E_prev = INFINITY;
+        *ctl = c;
+    }
+    for (long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x; r < S; r += (long long)gridDim.x * blockDim.x) {
+        int p[3];
+        shell_site((unsigned)r, g, p[0], p[1], p[2]);
+        bool inside = true, own = true;
+        int q[3];  // padded index of the nearest lattice site
         for (int d = 0; d < 3; ++d) {
-            own = own && p[d] >= 4 && p[d] < 4 + g.e[d];
             const int gl = p[d] + g.org[d] - 4;  // lattice site
             inside = inside && gl >= 0 && gl < g.n[d];
-            q[d] = min(max(gl, 0), g.n[d] - 1) - g.org[d] + 4;  // padded index of the nearest lattice site
+            q[d] = min(max(gl, 0), g.n[d] - 1) - g.org[d] + 4;
+            own = own && q[d] >= 4 && q[d] < 4 + g.e[d];
         }
-        if (own) continue;
-        if (pass == 0 && inside) {
-            const long long r = shell_rank(x, y, z, P1, P2, g.e[0], g.e[1], g.e[2]);
-            for (int A = 0; A < 4; ++A) phi[at(A, x, y, z)] = shell[A * S + r];
-        } else if (pass == 1 && !inside) {
-            for (int A = 0; A < 4; ++A) phi[at(A, x, y, z)] = phi[at(A, q[0], q[1], q[2])];
-        }
+        const long long from = inside ? r : own ? 0 : shell_rank(q[0], q[1], q[2], P1, P2, g.e[0], g.e[1], g.e[2]);
+        for (int A = 0; A < 4; ++A)
+            phi[at(A, p[0], p[1], p[2])] = !inside && own ? phi[at(A, q[0], q[1], q[2])] : shell[A * S + from];
     }
 }
 
-// the control block of one block step: no decision taken (the caller's), state as given
-__global__ void block_ctl_kernel(Ctl* __restrict__ ctl, int redo, int renorm64, int nblocks)
-{
-    if (threadIdx.x != 0) return;
-    Ctl c{};
-    c.redo = redo;
-    c.renorm64_every = renorm64 ? 1 : 0;
-    c.nblocks = nblocks;
-    c.hold = 1;
-    c.target = INT64_MAX;
-    c.E_prev = INFINITY;
-    *ctl = c;
-}
-
-// out = {E, E2, E4, E0, E6, power, max_force}
-__global__ void block_sums_kernel(const double* __restrict__ part, int nblocks, double h, int step,
-                                  double* __restrict__ out)
+// of a gradient sweep: out = {E, E2, E4, E0, E6, power, max_force}
+__global__ void block_sums_kernel(const double* __restrict__ part, int nblocks, double h, double* __restrict__ out)
 {
     double s[NRED];
     reduce_partials(part, nblocks, s);
     if (threadIdx.x == 0) {
         const double h3 = h * h * h;
         const double E2 = h3 * s[P_E2], E4 = h3 * s[P_E4], E0 = h3 * s[P_E0], E6 = h3 * s[P_E6];
-        out[0] = E2 + E4 + E0 + E6;  // in step mode the whole density is summed in the first slot
-        out[1] = step ? 0.0 : E2;
+        out[0] = E2 + E4 + E0 + E6;
+        out[1] = E2;
         out[2] = E4;
         out[3] = E0;
         out[4] = E6;
@@ -1511,19 +1542,6 @@ static skyr_status block_sweep_impl(const skyr_block* blk, skyr_precision prec, 
         if (sums) *sums = skyr_block_sums{};
         return SKYR_OK;
     }
-    // the shell
-    {
-        const int blocks = (int)std::min<long long>((g.sites() + 255) / 256, 8192);
-        for (int pass = 0; pass < 2; ++pass) {
-            if (prec == SKYR_F64)
-                hipLaunchKernelGGL(block_shell_kernel<double>, dim3(blocks), dim3(256), 0, s, (double*)phi,
-                                   (const double*)shell, g, pass, lead, pitch);
-            else
-                hipLaunchKernelGGL(block_shell_kernel<float>, dim3(blocks), dim3(256), 0, s, (float*)phi,
-                                   (const float*)shell, g, pass, lead, pitch);
-            SKYR_HIP(hipGetLastError());
-        }
-    }
     const Launch L = plan_block(g, prec);
     SweepArgs a;
     std::memset(&a, 0, sizeof a);
@@ -1572,19 +1590,37 @@ static skyr_status block_sweep_impl(const skyr_block* blk, skyr_precision prec, 
         a.vel = vel;
         a.ctl = ctl;
         a.stream = field_policy(prec, pitch > 0 ? (long long)g.P[0] * g.P[1] * pitch : g.sites(), pitch > 0 ? pitch : g.P[2]);
-        hipLaunchKernelGGL(block_ctl_kernel, dim3(1), dim3(64), 0, s, ctl, redo ? 1 : 0,
-                           (prec == SKYR_F32_BULK && renorm64) ? 1 : 0, L.blocks());
-        SKYR_HIP(hipGetLastError());
     } else {
         a.grad = out;
         a.projected = projected ? 1 : 0;
     }
+    {
+        const int blocks = (int)std::min<long long>((g.shell() + 255) / 256, 8192);
+        const int r64 = (prec == SKYR_F32_BULK && renorm64) ? 1 : 0;
+        if (prec == SKYR_F64)
+            hipLaunchKernelGGL(block_shell_kernel<double>, dim3(blocks), dim3(256), 0, s, (double*)phi,
+                               (const double*)shell, g, lead, pitch, a.ctl, redo ? 1 : 0, r64, L.blocks());
+        else
+            hipLaunchKernelGGL(block_shell_kernel<float>, dim3(blocks), dim3(256), 0, s, (float*)phi,
+                               (const float*)shell, g, lead, pitch, a.ctl, redo ? 1 : 0, r64, L.blocks());
+        SKYR_HIP(hipGetLastError());
+    }
     SKYR_HIP(timing_mark(s));
     SKYR_HIP(sweep(prec, step ? MODE_STEP : MODE_GRAD, L, a, s));
     SKYR_HIP(timing_mark(s));
-    if (sums) {
-        hipLaunchKernelGGL(block_sums_kernel, dim3(1), dim3(256), 0, s, a.partials, L.blocks(), blk->lattice.h,
-                           step ? 1 : 0, res);
+    if (sums && step) {
+        // a held step sweep's last block leaves its sums in the control block
+        Ctl c;
+        SKYR_HIP(hipMemcpyAsync(&c, ctl, sizeof c, hipMemcpyDeviceToHost, s));
+        SKYR_HIP(hipStreamSynchronize(s));
+        SKYR_HIP(timing_collect());
+        const double h3 = blk->lattice.h * blk->lattice.h * blk->lattice.h;
+        *sums = skyr_block_sums{};
+        sums->E = h3 * c.E;
+        sums->power = h3 * c.P;
+        sums->max_force = c.max_force;
+    } else if (sums) {
+        hipLaunchKernelGGL(block_sums_kernel, dim3(1), dim3(256), 0, s, a.partials, L.blocks(), blk->lattice.h, res);
         SKYR_HIP(hipGetLastError());
         double o[7];
         SKYR_HIP(hipMemcpyAsync(o, res, sizeof o, hipMemcpyDeviceToHost, s));

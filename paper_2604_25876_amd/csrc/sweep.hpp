@@ -1110,7 +1110,8 @@ template <bool MAX> __device__ __forceinline__ double wave_total(double v)
 // finishes last (a ticket counter in the control block, no waiting) sums them all in a
 // fixed order (thread t takes blocks t, t + THREADS, ..., then a fixed butterfly per wave
 // and the waves in order) and takes the flow's decision.  A restore sweep only clears the
-// restore flag; a sweep on a held control block only resets the ticket.
+// restore flag; a sweep on a held control block leaves the sums themselves there (E and P without
+// the factor h^3) and takes no decision.
 // The partial sums are agent-scope atomic stores of wave 0, complete (s_waitcnt) before the
 // block's ticket, and the last block reads them with agent-scope atomic loads: they are coherent
 // across the XCDs' L2 caches without a device-wide fence, which would write back and
@@ -1132,9 +1133,9 @@ __device__ __forceinline__ void finish_step(const double* part, int nb, Ctl* ctl
     }
     __syncthreads();
     if (!sm.last) return;
-    if (restore || ctl->hold) {
+    if (restore) {
         if (tid == 0) {
-            if (restore) ctl->restore = RESTORE_NONE;
+            ctl->restore = RESTORE_NONE;
             __hip_atomic_store(&ctl->ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         return;
@@ -1168,7 +1169,13 @@ __device__ __forceinline__ void finish_step(const double* part, int nb, Ctl* ctl
             f2 = fmax(f2, sm.red[w][1]);
             pw += sm.red[w][2];
         }
-        flow_decide(e, f2, pw, c, ctl);
+        if (c.hold) {
+            ctl->E = e;
+            ctl->P = pw;
+            ctl->max_force = sqrt(f2);
+        } else {
+            flow_decide(e, f2, pw, c, ctl);
+        }
         __hip_atomic_store(&ctl->ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
@@ -1284,7 +1291,6 @@ __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, S
     k.init(a, MODE == MODE_STEP);
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tiles = a.tiles_y * a.tiles_z;
     const int x0 = a.olo[0], nx = a.ohi[0] - a.olo[0] + 1;
