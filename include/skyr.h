@@ -421,7 +421,8 @@ SKYR_API skyr_status skyr_kinetic_energy(const skyr_lattice* lat, skyr_precision
  * normalisation of the Lagrangian, integrals as h^3 sums over the interior I
  * with a_i the fourth-order first differences, coordinates x = (idx - (n-1)/2) h:
  *   B       h^3 sum b (charge density b as in skyr_obs)
- *   E       the total static energy in the printed normalisation (2 x skyr_obs.E)
+ *   E       the total static energy in the printed normalisation (2 x skyr_obs.E, summed
+ *           in double from the stored field)
  *   X       centre of mass, (1/B) h^3 sum x b (eq. CoM); r = x - X below
  *   R       RMS radius, ((1/B) h^3 sum |r|^2 b)^(1/2) (eq. RMS radius)
  *   U, V, W isospin, spin and mixed inertia tensors (eqs. U, V, W inertia tensor),
@@ -438,9 +439,9 @@ typedef struct {
     double D;
 } skyr_moment_obs;
 
-/* Compute skyr_moment_obs of phi: one observables sweep for E, then two FP64
- * passes over I (the charge and its first moments, then the tensor densities in
- * the centre-of-mass frame), reduced in a fixed order on the device.
+/* Compute skyr_moment_obs of phi: two FP64 passes over I (the charge, its first
+ * moments and the energy, then the tensor densities in the centre-of-mass frame),
+ * reduced in a fixed order on the device.
  *   work  device workspace of skyr_workspace_bytes(lat, prec) bytes
  * Returns SKYR_E_NONFINITE, with *out filled, when |B| < 1e-6 (no centre of
  * mass) or a result is not finite.  Synchronises `stream`. */

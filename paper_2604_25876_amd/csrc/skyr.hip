@@ -977,9 +977,6 @@ skyr_status skyr_moments(const skyr_lattice* lat, skyr_precision prec, const sky
     if (st != SKYR_OK) return st;
     if (!out) return fail(SKYR_E_INVAL, "out must be non-null");
     hipStream_t s = (hipStream_t)stream;
-    double o[8];
-    st = run_gradient(lat, prec, model, phi, nullptr, 0, 1, o, work, s);  // E on the device at obs[0]
-    if (st != SKYR_OK) return st;
     char* w = (char*)work;
     MomArgs m;
     m.phi = phi;
@@ -988,24 +985,31 @@ skyr_status skyr_moments(const skyr_lattice* lat, skyr_precision prec, const sky
     m.n2 = lat->n[2];
     m.h = lat->h;
     m.partials = (double*)(w + CTL_BYTES + OBS_BYTES);
-    m.obs = (const double*)(w + CTL_BYTES);
+    m.m = model->m;
+    m.m_y = model->m_y;
+    m.m_z = model->m_z;
+    m.m_w = model->m_w;
+    m.c6 = model->c6;
     m.centre = (double*)(w + CTL_BYTES + MOM_CENTRE_OFFSET);
     m.out = (double*)(w + CTL_BYTES + MOM_OUT_OFFSET);
-    const long long nI = (long long)(lat->n[0] - 4) * (lat->n[1] - 4) * (lat->n[2] - 4);
-    const int nb = (int)std::min<long long>(MOM_MAX_BLOCKS, (nI + MOM_THREADS - 1) / MOM_THREADS);
+    const long long pairs = (long long)(lat->n[0] - 4) * (lat->n[1] - 4) * ((lat->n[2] - 3) / 2);
+    const long long most = (pairs + MOM_THREADS - 1) / MOM_THREADS;
+    // at least one block per XCD: each walks an eighth of the lattice
+    const int nb1 = (int)std::max<long long>(8, std::min<long long>(MomAcc<MOM_PASS_CENTRE>::MAX_BLOCKS, most));
+    const int nb2 = (int)std::max<long long>(8, std::min<long long>(MomAcc<MOM_PASS_TENSORS>::MAX_BLOCKS, most));
     if (prec == SKYR_F64)
-        hipLaunchKernelGGL((moments_kernel<double, MOM_PASS_CENTRE>), dim3(nb), dim3(MOM_THREADS), 0, s, m);
+        hipLaunchKernelGGL((moments_kernel<double, MOM_PASS_CENTRE>), dim3(nb1), dim3(MOM_THREADS), 0, s, m);
     else
-        hipLaunchKernelGGL((moments_kernel<float, MOM_PASS_CENTRE>), dim3(nb), dim3(MOM_THREADS), 0, s, m);
+        hipLaunchKernelGGL((moments_kernel<float, MOM_PASS_CENTRE>), dim3(nb1), dim3(MOM_THREADS), 0, s, m);
     SKYR_HIP(hipGetLastError());
-    hipLaunchKernelGGL(moments_centre_kernel, dim3(1), dim3(MOM_THREADS), 0, s, m, nb);
+    hipLaunchKernelGGL(moments_centre_kernel, dim3(1), dim3(MOM_FINISH_THREADS), 0, s, m, nb1);
     SKYR_HIP(hipGetLastError());
     if (prec == SKYR_F64)
-        hipLaunchKernelGGL((moments_kernel<double, MOM_PASS_TENSORS>), dim3(nb), dim3(MOM_THREADS), 0, s, m);
+        hipLaunchKernelGGL((moments_kernel<double, MOM_PASS_TENSORS>), dim3(nb2), dim3(MOM_THREADS), 0, s, m);
     else
-        hipLaunchKernelGGL((moments_kernel<float, MOM_PASS_TENSORS>), dim3(nb), dim3(MOM_THREADS), 0, s, m);
+        hipLaunchKernelGGL((moments_kernel<float, MOM_PASS_TENSORS>), dim3(nb2), dim3(MOM_THREADS), 0, s, m);
     SKYR_HIP(hipGetLastError());
-    hipLaunchKernelGGL(moments_finish_kernel, dim3(1), dim3(MOM_THREADS), 0, s, m, nb);
+    hipLaunchKernelGGL(moments_finish_kernel, dim3(1), dim3(MOM_FINISH_THREADS), 0, s, m, nb2);
     SKYR_HIP(hipGetLastError());
     SKYR_HIP(hipMemcpyAsync(out, m.out, sizeof(skyr_moment_obs), hipMemcpyDeviceToHost, s));
     SKYR_HIP(hipStreamSynchronize(s));
