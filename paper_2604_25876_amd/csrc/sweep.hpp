@@ -677,10 +677,15 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT, int STREAM> s
         }
         if (out && j_out) {
             const T e2 = k.ke2 * cl;
-            const T e4 = k.ke4 * (gxx * gyy + gxx * gzz + gyy * gzz - gxy * gxy - gxz * gxz - gyz * gyz);
+            const T quartic = gxx * gyy + gxx * gzz + gyy * gzz - gxy * gxy - gxz * gxz - gyz * gyz;
+            const T e4 = k.ke4 * quartic;
             const T e0 = potential(c[0]);
             if constexpr (MODE == MODE_STEP) {
-                pe2 += (double)(e2 + e4 + e0 + e6);  // the flow needs the total energy only
+                // The flow needs the total energy only.  In single precision it is written out which of
+                // the two products is rounded: left to the compiler it changed with the code around it,
+                // and with it the energy of a field by some 1e-10.
+                const T e24 = sizeof(T) == 4 ? fmaT(k.ke4, quartic, e2) : e2 + e4;
+                pe2 += (double)(e24 + e0 + e6);
             } else {
                 pe2 += (double)e2;
                 pe4 += (double)e4;
