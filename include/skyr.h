@@ -453,15 +453,15 @@ SKYR_API skyr_status skyr_moments(const skyr_lattice* lat, skyr_precision prec, 
  * a kernel and form one chain; per sweep slot a chain is one launch over its
  * fields' tiles, whose blocks also take each field's flow decision (the last
  * block of a field to finish reads its partial sums).  The launch's blocks are
- * laid out for the device: a field's blocks in pieces of at most one XCD's
- * compute units, the pieces spread over the XCDs by estimated work and the
+ * laid out for the device: a field's blocks in pieces of a few neighbours,
+ * the pieces spread over the XCDs by estimated work and the
  * longest blocks dispatched first.  Chains share no field: skyr_batch_run
  * replays a captured hipGraph of `sweeps` slots that runs the chains as
- * independent branches.  A field's blocks, partial sums and decisions are
- * those of the same field flowing alone with its lattice's batch tile (see
- * skyr_get_batch_tile), so a field's result does not depend on the other
- * fields in the batch, and equals that of skyr_anf_step when skyr_set_tile
- * gives the lattice the same tile.  A batch object owns only its job table,
+ * independent branches.  Fields on default batch tiles are cut along x as the
+ * load asks, few fields into short slabs and many into long ones, but their
+ * sums are kept per unit of at most 16 planes in an order of their own, so a
+ * field's result does not depend on the other fields in the batch (it is the
+ * same bytes).  It equals that of skyr_anf_step up to the order of the sums.  A batch object owns only its job table,
  * control blocks and graph; field, velocity and workspace memory stay with
  * the caller and must stay valid while the field is in the batch.  A batch is
  * used by one thread at a time.
@@ -526,8 +526,9 @@ SKYR_API skyr_status skyr_batch_destroy(skyr_batch* b);
  * tile setting of their own (skyr_set_batch_tile, skyr_batch_autotune) whose
  * default is the precision's first shape (variant 0: the fields of one
  * precision then share one launch per sweep slot) with x split evenly into the
- * fewest slabs of at most 64 planes: in a batch the other fields fill the
- * device.  The getters report the setting in force, the default included. */
+ * fewest slabs of at most 64 planes; as with a single field that default is what
+ * is reported, and the batch launches the slabs that suit its load (see above).
+ * A batch tile set to another choice is used as it was set.  The getters report the setting in force, the default included. */
 SKYR_API int32_t skyr_tile_variants(skyr_precision prec);
 SKYR_API skyr_status skyr_tile_variant_info(skyr_precision prec, int32_t variant, int32_t info[3]);
 SKYR_API skyr_status skyr_set_tile(const skyr_lattice* lat, skyr_precision prec, int32_t variant, int32_t xchunk);

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <functional>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -86,6 +87,10 @@ struct Launch {
     int variant;
     Shape shape;
     int xchunk;  // planes per slab
+    // in batches: the units of planes that partial sums are kept for, and units per slab; a batch
+    // chooses per_block where free_slabs
+    int units, per_block;
+    bool free_slabs;
     int tiles_z, tiles_y, zstart, slabs;
     int blocks() const { return tiles_z * tiles_y * slabs; }
     int threads() const { return shape.threads(); }
@@ -124,6 +129,8 @@ static Launch plan_with(const skyr_lattice* lat, skyr_precision prec, int varian
     tile_grid(lat, L.shape, L.tiles_y, L.tiles_z, L.zstart);
     const int nx = lat->n[0] - 4;
     L.slabs = (nx + xchunk - 1) / xchunk;
+    L.units = L.slabs;
+    L.per_block = 1;
     return L;
 }
 
@@ -250,8 +257,8 @@ static std::pair<int, int> tile_in_force(const skyr_lattice* lat, skyr_precision
     return {v, xc};
 }
 
-// Tile shape and slab length of a field in a batch on a lattice that no one has set or
-// tuned for batches.  The shape is the precision's first: fields of one precision then
+// Tile shape and slab length of a field in a batch, as skyr_get_batch_tile reports them, on a lattice
+// that no one has set or tuned for batches (batch_slabs cuts x as the load asks).  The shape is the precision's first: fields of one precision then
 // share one launch per sweep slot (fields of other shapes run as concurrent launches,
 // which mix their blocks on the CUs so that a field's neighbouring tiles no longer march
 // together; each extra launch cost the 64-field mix a few percent).  The batch's other
@@ -268,19 +275,40 @@ static void batch_default_tile(const skyr_lattice* lat, skyr_precision prec, int
     xc_out = std::max(std::min(kMinChunk, nx), (nx + slabs - 1) / slabs);
 }
 
+// Launch of a field on its default batch tile.  The batch cuts x into slabs of whole units, as long
+// or short as its load asks (batch_slabs); the field's sums are kept per unit, of at most kMinChunk
+// planes (as many records as every workspace holds), and do not depend on the slabs.
+static Launch batch_default_launch(const skyr_lattice* lat, skyr_precision prec, int v, int xc)
+{
+    Launch L = plan_with(lat, prec, v, xc);
+    const int nx = lat->n[0] - 4;
+    L.units = std::min(nx, 2 * ((nx + 2 * kMinChunk - 1) / (2 * kMinChunk)));
+    L.per_block = (L.units + L.slabs - 1) / L.slabs;
+    L.free_slabs = true;
+    return L;
+}
+
 static Launch plan_batch(const skyr_lattice* lat, skyr_precision prec)
 {
     int v = 0, xc = 0;
+    batch_default_tile(lat, prec, v, xc);
     {
         std::lock_guard<std::mutex> g(g_tile_mu);
         auto it = g_batch_tiles.find(TileKey{lat->n[0], lat->n[1], lat->n[2], (int)prec});
-        if (it != g_batch_tiles.end()) {
-            v = it->second.first;
-            xc = it->second.second;
-        }
+        if (it != g_batch_tiles.end() && it->second != std::make_pair(v, xc))
+            return plan_with(lat, prec, it->second.first, it->second.second);
     }
-    if (xc == 0) batch_default_tile(lat, prec, v, xc);
-    return plan_with(lat, prec, v, xc);
+    return batch_default_launch(lat, prec, v, xc);
+}
+
+// Cut a field into slabs of whole units of at most `cap` planes (one unit at least), as even as the
+// units allow.
+static void cut_slabs(Launch& L, int nx, int cap)
+{
+    const int most = std::max(1, std::min(MAX_UNITS, cap * L.units / nx));
+    L.slabs = (L.units + most - 1) / most;
+    L.per_block = (L.units + L.slabs - 1) / L.slabs;
+    L.slabs = (L.units + L.per_block - 1) / L.per_block;
 }
 
 // The printed-form sweep: its fixed tile shape, one block per (slab, tile) item, and the
@@ -592,6 +620,8 @@ static SweepArgs make_args(const skyr_lattice* lat, const Launch& L, const skyr_
     a.tiles_y = L.tiles_y;
     a.zstart = L.zstart;
     a.xchunk = L.xchunk;
+    a.units = L.units;
+    a.per_block = L.per_block;
     a.h = lat->h;
     a.m = model->m;
     a.m_y = model->m_y;
@@ -1959,25 +1989,38 @@ static skyr_status upload_ints(const std::vector<int>& v, int*& d, int& cap)
     return SKYR_OK;
 }
 
+// planes of slab `slab` of a field in a batch
+static int slab_planes(const Launch& L, int nx, int slab)
+{
+    const int first = slab * L.per_block, end = std::min(L.units, first + L.per_block);
+    return end * nx / L.units - first * nx / L.units;
+}
+
 // Sweep time of block `blk` of a job, in the units of a shape's cost factor: the planes
-// of its item (the march's four extra included) times the item's output columns.
+// of its item (with what a block pays on top) times the item's output columns.
 static double item_time(const Launch& L, int nx, int blk)
 {
     const int tiles = L.tiles_y * L.tiles_z;
-    const int slab = blk / tiles;
-    const int planes = std::min(L.xchunk, nx - slab * L.xchunk);
-    return (double)(planes + 4) * L.shape.oy() * L.shape.oz() * L.shape.cost;
+    const int planes = slab_planes(L, nx, blk / tiles);
+    return (double)(planes + 6) * L.shape.oy() * L.shape.oz() * L.shape.cost;
 }
 
-// The launch slots of one chain.  Blocks go to the XCDs in pieces of at most one XCD's
-// CUs from one job (a job's neighbouring tiles then march through the same planes on
+constexpr int kXcds = 8;
+// Blocks of a field that stay together on one XCD, whose L2 then serves the halos of neighbouring
+// tiles.  Smaller pieces spread the work more evenly: pieces of a whole XCD (32) left the twelve-field
+// scan 28% behind at its best slab length.  With two chains, whose blocks mix on the CUs anyway, 8 are
+// better still (20 mixed fields 60.1 -> 58.9 ms); with one, 16 (twelve fields 6.92 ms against 7.25).
+static int piece_blocks(int chains) { return chains > 1 ? 8 : 16; }
+
+// The launch slots of one chain.  Blocks go to the XCDs in pieces of at most piece_blocks blocks
+// from one job (a job's neighbouring tiles then march through the same planes on
 // one L2), the piece of most work first, each to the XCD with the least work so far;
 // on each XCD, the pieces with the longest blocks dispatch first.  Launch block p runs
 // on XCD p mod 8 as the (p / 8)-th block there; XCDs with fewer blocks are padded with
 // empty slots.
-static std::vector<int> chain_slots(const skyr_batch* b, const std::vector<int>& jobs, const std::vector<int>& count)
+static std::vector<int> chain_slots(const skyr_batch* b, const std::vector<int>& jobs, const std::vector<int>& count,
+                                    int piece)
 {
-    constexpr int kXcds = 8, kPiece = kCUs / kXcds;
     struct Piece {
         int job, first, n;
         double work, longest;
@@ -1986,8 +2029,8 @@ static std::vector<int> chain_slots(const skyr_batch* b, const std::vector<int>&
     for (int j : jobs) {
         const auto& J = b->jobs[j];
         const int nx = J.lat.n[0] - 4;
-        for (int f = 0; f < count[j]; f += kPiece) {
-            Piece pc{j, f, std::min(kPiece, count[j] - f), 0.0, 0.0};
+        for (int f = 0; f < count[j]; f += piece) {
+            Piece pc{j, f, std::min(piece, count[j] - f), 0.0, 0.0};
             for (int k = f; k < f + pc.n; ++k) {
                 const double t = item_time(J.L, nx, k);
                 pc.work += t;
@@ -2024,11 +2067,112 @@ static std::vector<int> chain_slots(const skyr_batch* b, const std::vector<int>&
     return slots;
 }
 
+// Estimated time of a sweep slot with the fields cut as `cut` has them (microseconds): the blocks go
+// to the XCDs in pieces as chain_slots deals them out, and on an XCD, longest first, each to the CU
+// that is free first.  A block takes its planes and about six more times its shape's step time.
+// Beyond kSimulated blocks, where one block weighs little, the work spread over all CUs and half a
+// longest block for the end of the launch: the choice is then among long slabs, and cheap on the host.
+constexpr int kSimulated = 2048;
+static double slot_time(const skyr_batch* b, const std::vector<Launch>& cut)
+{
+    constexpr int kPerXcd = kCUs / kXcds;
+    struct Piece {
+        double t;
+        int n;
+    };
+    std::vector<Piece> of_group[skyr_batch::kGroups];
+    bool used[skyr_batch::kGroups] = {};
+    int chains = 0;
+    for (int j = 0; j < b->max_jobs; ++j)
+        if (b->jobs[j].active) {
+            bool& u = used[batch_group(b->jobs[j].prec, cut[j].variant)];
+            chains += u ? 0 : 1;
+            u = true;
+        }
+    const int piece = piece_blocks(chains);
+    double total = 0.0, longest = 0.0;
+    int blocks = 0;
+    for (int j = 0; j < b->max_jobs; ++j) {
+        const auto& J = b->jobs[j];
+        if (!J.active) continue;
+        const Launch& L = cut[j];
+        const int tiles = L.tiles_y * L.tiles_z;
+        const double step = J.prec == SKYR_F64 ? kStepF64[L.variant] : kStepF32[L.variant];
+        for (int sl = 0; sl < L.slabs; ++sl) {
+            const double t = (slab_planes(L, J.lat.n[0] - 4, sl) + 6) * step;
+            for (int n = tiles; n > 0; n -= piece)
+                of_group[batch_group(J.prec, L.variant)].push_back({t, std::min(n, piece)});
+            total += t * tiles;
+            longest = std::max(longest, t);
+        }
+        blocks += L.blocks();
+    }
+    if (blocks > kSimulated) return total / kCUs + 0.5 * longest;
+    std::vector<Piece> on[kXcds];
+    for (auto& pieces : of_group) {
+        std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& x, const Piece& y) { return x.t * x.n > y.t * y.n; });
+        double load[kXcds] = {};
+        for (const Piece& p : pieces) {
+            const int x = (int)(std::min_element(load, load + kXcds) - load);
+            load[x] += p.t * p.n;
+            on[x].push_back(p);
+        }
+    }
+    double end = 0.0;
+    for (auto& pieces : on) {
+        std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& x, const Piece& y) { return x.t > y.t; });
+        std::vector<double> cu(kPerXcd, 0.0);  // a heap, the CU that is free first on top
+        for (const Piece& p : pieces)
+            for (int k = 0; k < p.n; ++k) {
+                std::pop_heap(cu.begin(), cu.end(), std::greater<double>());
+                cu.back() += p.t;
+                end = std::max(end, cu.back());
+                std::push_heap(cu.begin(), cu.end(), std::greater<double>());
+            }
+    }
+    return end;
+}
+
+// Cut the fields on default tiles into slabs for the load as it is: the longest (by kMinChunk planes)
+// unless shorter ones are estimated to take 1% less.  A block pays for six planes more than it
+// writes, so a full device wants long slabs and an idle one short ones; the slabs of at most 64
+// planes that every batch had fit neither.  Flows of 24 steps, in ms: two fields of 64 and 128 sites
+// 2.62 -> 1.65, five mixed fields 3.50 -> 2.80, 24 of the scan 9.76 -> 9.28; of 48 steps: 64 of the
+// scan 48.5 -> 46.9, 20 mixed ones 60.8 -> 59.3.
+static void batch_slabs(skyr_batch* b)
+{
+    std::vector<Launch> best, cut(b->max_jobs), before;
+    double least = INFINITY;
+    for (int cap = MAX_UNITS * kMinChunk; cap >= kMinChunk; cap -= kMinChunk) {
+        bool differs = before.empty();
+        for (int j = 0; j < b->max_jobs; ++j) {
+            const auto& J = b->jobs[j];
+            if (!J.active) continue;
+            cut[j] = J.L;
+            if (J.L.free_slabs) cut_slabs(cut[j], J.lat.n[0] - 4, cap);
+            differs = differs || cut[j].slabs != before[j].slabs;
+        }
+        if (!differs) continue;
+        before = cut;
+        const double t = slot_time(b, cut);
+        if (t < 0.99 * least) {
+            least = t;
+            best = cut;
+        }
+    }
+    for (int j = 0; j < b->max_jobs; ++j)
+        if (b->jobs[j].active) {
+            b->jobs[j].L = best[j];
+            b->args[j].per_block = best[j].per_block;
+        }
+}
+
 // rebuild the device job tables, chains and launch slots from the host description
 static skyr_status batch_rebuild(skyr_batch* b)
 {
     std::vector<int> count(b->max_jobs, 0), of_group[skyr_batch::kGroups];
     long long bytes = 0;
+    batch_slabs(b);
     for (int j = 0; j < b->max_jobs; ++j) {
         const auto& J = b->jobs[j];
         if (!J.active) continue;
@@ -2050,7 +2194,7 @@ static skyr_status batch_rebuild(skyr_batch* b)
     for (int c = 0; c < skyr_batch::kChains; ++c) {
         b->ext[c] = EXT_NONE;
         for (int j : list[c]) b->ext[c] = std::max(b->ext[c], ext_level(b->args[j]));
-        const std::vector<int> slots = chain_slots(b, list[c], count);
+        const std::vector<int> slots = chain_slots(b, list[c], count, piece_blocks(nc));
         skyr_status rc = upload_ints(slots, b->d_map[c], b->map_cap[c]);
         if (rc != SKYR_OK) return rc;
         b->grid[c] = (int)slots.size() / 2;
@@ -2339,7 +2483,9 @@ static skyr_status batch_settle(skyr_batch* b, int j)
     if (h.restore) {
         const auto& J = b->jobs[j];
         const SweepArgs& a = b->args[j];
-        SKYR_HIP(sweep(J.prec, MODE_STEP, J.L, a, b->stream));
+        Launch L = J.L;  // slabs of xchunk planes, as a launch of the field alone has them
+        L.slabs = (J.lat.n[0] - 4 + L.xchunk - 1) / L.xchunk;
+        SKYR_HIP(sweep(J.prec, MODE_STEP, L, a, b->stream));
         SKYR_HIP(hipMemcpyAsync(&h, a.ctl, sizeof h, hipMemcpyDeviceToHost, b->stream));
         SKYR_HIP(hipStreamSynchronize(b->stream));
     }
@@ -2474,7 +2620,8 @@ skyr_status skyr_batch_autotune(const skyr_lattice* lat, skyr_precision prec, co
         if (cands[i].v == dv && cands[i].xc == dx) di = i;
     const long long array_sites = pitch > 0 ? (long long)lat->n[0] * lat->n[1] * pitch : sites(lat);
     for (Cand& cd : cands) {
-        const Launch L = plan_with(lat, prec, cd.v, cd.xc);
+        const bool is_default = di < cands.size() && &cd == &cands[di];  // timed as it is launched
+        const Launch L = is_default ? batch_default_launch(lat, prec, cd.v, cd.xc) : plan_with(lat, prec, cd.v, cd.xc);
         for (int i = 0; i < copies; ++i) {
             if (b->jobs[i].active && (rc = skyr_batch_remove(b, i)) != SKYR_OK) return done(rc);
             SKYR_HIP_OR(fill(vel[i], 4 * array_sites, prec, 0.0, s), done);

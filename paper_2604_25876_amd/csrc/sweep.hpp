@@ -118,6 +118,7 @@ struct SweepArgs {
     int tiles_z, tiles_y;  // output tiles of the (y, z) plane
     int zstart;            // z of the first tile's first column (at most olo[2]; below it for line-aligned tiles)
     int xchunk;            // planes per slab (the work order's outer unit)
+    int units, per_block;  // batched sweeps (instead of xchunk): units of planes, and units of one block
     int projected;     // MODE_GRAD: write g - (g.phi) phi instead of g
     int baryon;        // accumulate the baryon density
     double h, dt;
@@ -315,10 +316,18 @@ template <int NWI_, int NWH_, int HPT_, int OZ_> struct Geo {
     static_assert(NWH * 64 * HPT >= NHALO, "every halo position has a lane");
 };
 
+// A batched sweep keeps a field's sums per unit of planes; records of energy density, largest
+// |F|^2 and power, at most MAX_UNITS of them from one block.
+enum : int { U_E = 0, U_F2 = 1, U_POW = 2, UNIT_REC = 4 };
+constexpr int MAX_UNITS = 16;
+
 template <typename T, class G> struct SweepSmem {
     SitePlane<T, G::PPLANE> phi[2];     // [plane parity]
     SitePlane<T, 2 * G::QPLANE> q[2];   // [plane parity]: sites of Q_y, then those of Q_z
     double red[G::NW][NPART];
+    double unit[MAX_UNITS - 1][G::NWI][3];  // batched sweeps: the waves' sums over the units before the last
+    int unit_end[MAX_UNITS];                // and the ends of the block's units, in planes from its first
+    int units_ended[G::NWI];
     int last;  // this block is the last of its field to finish the sweep
 };
 
@@ -371,6 +380,78 @@ template <typename T> struct SweepConst {
     }
 };
 
+// v of another lane, by cross-lane moves of the vector unit (the shuffles of a butterfly went
+// through LDS, six dependent round trips a sum)
+template <int CTRL> __device__ __forceinline__ double dpp_f64(double v)
+{
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)u, CTRL, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+// The sum (maximum) of v over the wave, in every lane, in a fixed order: lanes 1 and 2 away, then
+// (the sums of all lanes of a quad being equal) the mirrored lanes of 8 and 16, then the lanes 16
+// and 32 away: a swap of two copies' halves leaves one half's sum in one copy and the other's in
+// the other.
+template <bool MAX> __device__ __forceinline__ double wave_total(double v)
+{
+    const auto add = [](double a, double b) { return MAX ? fmax(a, b) : a + b; };
+    v = add(v, dpp_f64<0xb1>(v));   // quad lanes 1, 0, 3, 2
+    v = add(v, dpp_f64<0x4e>(v));   // quad lanes 2, 3, 0, 1
+    v = add(v, dpp_f64<0x141>(v));  // mirrored in 8 lanes
+    v = add(v, dpp_f64<0x140>(v));  // mirrored in 16 lanes
+    const auto halves = [&](auto swap) {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        const auto lo = swap((unsigned)u), hi = swap((unsigned)(u >> 32));
+        const double x = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
+        const double y = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+        return add(x, y);
+    };
+    v = halves([](unsigned u) { return __builtin_amdgcn_permlane16_swap(u, u, false, false); });
+    v = halves([](unsigned u) { return __builtin_amdgcn_permlane32_swap(u, u, false, false); });
+    return v;
+}
+
+// a and b summed over the wave: a in lanes 0 .. 31, b in lanes 32 .. 63 from the first stage on
+// (two sums for little more than one); every lane of the lower half ends with a's, all with b's total
+__device__ __forceinline__ void wave_totals(double& a, double& b)
+{
+    const unsigned long long ua = __builtin_bit_cast(unsigned long long, a), ub = __builtin_bit_cast(unsigned long long, b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+    double v = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+               __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+    v += dpp_f64<0xb1>(v);
+    v += dpp_f64<0x4e>(v);
+    v += dpp_f64<0x141>(v);
+    v += dpp_f64<0x140>(v);
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)u, (unsigned)u, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
+    v = __builtin_bit_cast(double, ((unsigned long long)h[0] << 32) | l[0]) +
+        __builtin_bit_cast(double, ((unsigned long long)h[1] << 32) | l[1]);
+    const unsigned long long w = __builtin_bit_cast(unsigned long long, v);
+    a = v;
+    b = __builtin_bit_cast(double, ((unsigned long long)__builtin_amdgcn_readlane((unsigned)(w >> 32), 32) << 32) |
+                                       (unsigned)__builtin_amdgcn_readlane((unsigned)w, 32));
+}
+// the largest of the non-negative v over the wave, in every lane
+__device__ __forceinline__ double wave_most(double v) { return wave_total<true>(v); }
+__device__ __forceinline__ float wave_most(float v)
+{
+    const auto other = [](float x, auto dpp) { return __builtin_bit_cast(float, dpp(__builtin_bit_cast(int, x))); };
+    v = fmaxf(v, other(v, [](int x) { return __builtin_amdgcn_mov_dpp(x, 0xb1, 0xf, 0xf, true); }));
+    v = fmaxf(v, other(v, [](int x) { return __builtin_amdgcn_mov_dpp(x, 0x4e, 0xf, 0xf, true); }));
+    v = fmaxf(v, other(v, [](int x) { return __builtin_amdgcn_mov_dpp(x, 0x141, 0xf, 0xf, true); }));
+    v = fmaxf(v, other(v, [](int x) { return __builtin_amdgcn_mov_dpp(x, 0x140, 0xf, 0xf, true); }));
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    v = fmaxf(__builtin_bit_cast(float, (unsigned)p[0]), __builtin_bit_cast(float, (unsigned)p[1]));
+    const unsigned t = __builtin_bit_cast(unsigned, v);
+    const auto q = __builtin_amdgcn_permlane32_swap(t, t, false, false);
+    return fmaxf(__builtin_bit_cast(float, (unsigned)q[0]), __builtin_bit_cast(float, (unsigned)q[1]));
+}
+
 // One item of a field's work: output planes [xa, xe) of tile (ty, tz).
 struct Segment {
     int ty, tz, xa, xe;
@@ -391,6 +472,9 @@ __device__ __forceinline__ Segment item_segment(int item, int tiles, int tiles_z
     s.xe = x0 + min(nx, (slab + 1) * xchunk);
     return s;
 }
+
+// first plane of unit k of a field's nx planes in `units` units of the same length (but one)
+__device__ __forceinline__ int unit_start(int k, int nx, int units) { return k * nx / units; }
 
 // Fields, flags and sums shared by the two roles.
 template <typename T, bool FROM_TABLE> struct SweepCommon {
@@ -457,6 +541,7 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT, int STREAM> s
     T vnxt[4];     // prefetched velocity of plane j-1
 
     double pe2 = 0.0, pe4 = 0.0, pe0 = 0.0, pe6 = 0.0, pb_sum = 0.0;
+    T elate[2] = {T(0), T(0)};  // batched sweeps: the energy density of planes j-1, j-2
     double pp = 0.0;  // scaled power F^ . v of the incoming velocity
     T pf2 = T(0);     // largest scaled |F^|^2
 
@@ -675,6 +760,7 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT, int STREAM> s
             acc[SM2][A] += qx[A];
             acc[SP2][A] -= qx[A];
         }
+        T ecur = T(0);
         if (out && j_out) {
             const T e2 = k.ke2 * cl;
             const T quartic = gxx * gyy + gxx * gzz + gyy * gzz - gxy * gxy - gxz * gxz - gyz * gyz;
@@ -685,7 +771,8 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT, int STREAM> s
                 // the two products is rounded: left to the compiler it changed with the code around it,
                 // and with it the energy of a field by some 1e-10.
                 const T e24 = sizeof(T) == 4 ? fmaT(k.ke4, quartic, e2) : e2 + e4;
-                pe2 += (double)(e24 + e0 + e6);
+                if constexpr (FROM_TABLE) ecur = e24 + e0 + e6;
+                else pe2 += (double)(e24 + e0 + e6);
             } else {
                 pe2 += (double)e2;
                 pe4 += (double)e4;
@@ -730,6 +817,7 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT, int STREAM> s
             for (int A = 0; A < 4; ++A) f[A] = fmaT(gp, p[A], -g[A]);  // F^ = (g^.phi) phi - g^
             pf2 = fmax_nonneg(pf2, dot4(f, f));
             if constexpr (MODE == MODE_STEP) {
+                if constexpr (FROM_TABLE) pe2 += (double)elate[1];
                 pp += (double)dot4(f, vcur);  // the product in the field precision, the sum in double
                 if (cm.restore) {
 #pragma unroll
@@ -773,7 +861,48 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT, int STREAM> s
         }
 #pragma unroll
         for (int A = 0; A < 4; ++A) acc[SM2][A] = T(0);  // the slot starts plane j+3
+        if constexpr (FROM_TABLE) {
+            elate[1] = elate[0];
+            elate[0] = ecur;
+        }
         __syncthreads();
+    }
+
+    // A block of a batched sweep marches through one or more units of planes and keeps the sums of
+    // each apart, so that a field's sums do not depend on how its planes are cut into blocks: when
+    // every unit but the last has ended, before step k units + 4, the wave's sums go to shared memory
+    // and start anew.  `ev` is the next such step or the end of the march, and all that the march
+    // itself looks at.  (The energy of a plane is added two planes late, with its force, so that a
+    // unit ends once.)  It costs 0.5% of the march at 16 planes a unit.
+    __device__ __forceinline__ bool at_event(int st, int& ev)
+    {
+        if constexpr (FROM_TABLE) {
+            int last = xe;  // (formed here, not kept through the march)
+            asm volatile("" : "+s"(last));
+            if (st >= last - xa + 4) return true;
+            const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+            const int k = __builtin_amdgcn_readfirstlane(sm.units_ended[wave]);
+            double e = pe2, p = pp;
+            wave_totals(e, p);
+            const T f = wave_most(pf2);
+            if ((threadIdx.x & 63) == 0) {
+                sm.unit[k][wave][U_E] = e;
+                sm.unit[k][wave][U_F2] = (double)f;
+                sm.unit[k][wave][U_POW] = p;
+                sm.units_ended[wave] = k + 1;
+            }
+            pe2 = pp = 0.0;
+            pf2 = T(0);
+            ev = next_event(k + 1);
+            return false;
+        } else {
+            return true;
+        }
+    }
+    // the step before which unit k has ended, or the end of the march for the last
+    __device__ __forceinline__ int next_event(int k) const
+    {
+        return __builtin_amdgcn_readfirstlane(sm.unit_end[k]) + 4;
     }
 
     // the march over one segment
@@ -800,17 +929,19 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT, int STREAM> s
         sm.phi[0].st(pidx + PO, ring[2]);
         __syncthreads();
         const int nst = (xe - xa) + 4;
-        for (int st = 0; st < nst; st += 5) {
+        int ev = FROM_TABLE ? next_event(0) : nst;
+        for (int st = 0;; st += 5) {
             const int j = js + st, pb = st & 1;
             step<0>(j, pb);
-            if (st + 1 >= nst) break;
+            if (st + 1 >= ev && at_event(st + 1, ev)) break;
             step<1>(j + 1, pb ^ 1);
-            if (st + 2 >= nst) break;
+            if (st + 2 >= ev && at_event(st + 2, ev)) break;
             step<2>(j + 2, pb);
-            if (st + 3 >= nst) break;
+            if (st + 3 >= ev && at_event(st + 3, ev)) break;
             step<3>(j + 3, pb ^ 1);
-            if (st + 4 >= nst) break;
+            if (st + 4 >= ev && at_event(st + 4, ev)) break;
             step<4>(j + 4, pb);
+            if (st + 5 >= ev && at_event(st + 5, ev)) break;
         }
     }
 };
@@ -1079,41 +1210,9 @@ __device__ inline void flow_decide(double sum_e, double max_f2, double sum_pow, 
     }
 }
 
-// v of another lane, by cross-lane moves of the vector unit (the shuffles of a butterfly went
-// through LDS, six dependent round trips a sum)
-template <int CTRL> __device__ __forceinline__ double dpp_f64(double v)
-{
-    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)u, CTRL, 0xf, 0xf, true);
-    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-// The sum (maximum) of v over the wave, in every lane, in a fixed order: lanes 1 and 2 away, then
-// (the sums of all lanes of a quad being equal) the mirrored lanes of 8 and 16, then the lanes 16
-// and 32 away: a swap of two copies' halves leaves one half's sum in one copy and the other's in
-// the other.
-template <bool MAX> __device__ __forceinline__ double wave_total(double v)
-{
-    const auto add = [](double a, double b) { return MAX ? fmax(a, b) : a + b; };
-    v = add(v, dpp_f64<0xb1>(v));   // quad lanes 1, 0, 3, 2
-    v = add(v, dpp_f64<0x4e>(v));   // quad lanes 2, 3, 0, 1
-    v = add(v, dpp_f64<0x141>(v));  // mirrored in 8 lanes
-    v = add(v, dpp_f64<0x140>(v));  // mirrored in 16 lanes
-    const auto halves = [&](auto swap) {
-        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-        const auto lo = swap((unsigned)u), hi = swap((unsigned)(u >> 32));
-        const double x = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
-        const double y = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
-        return add(x, y);
-    };
-    v = halves([](unsigned u) { return __builtin_amdgcn_permlane16_swap(u, u, false, false); });
-    v = halves([](unsigned u) { return __builtin_amdgcn_permlane32_swap(u, u, false, false); });
-    return v;
-}
-
 // End of a step sweep: every block has published its partial sums; the block that
 // finishes last (a ticket counter in the control block, no waiting) sums them all in a
-// fixed order (thread t takes blocks t, t + THREADS, ..., then a fixed butterfly per wave
+// fixed order (thread t takes records t, t + THREADS, ..., then a fixed butterfly per wave
 // and the waves in order) and takes the flow's decision.  A restore sweep only clears the
 // restore flag; a sweep on a held control block leaves the sums themselves there (E and P without
 // the factor h^3) and takes no decision.
@@ -1126,8 +1225,9 @@ template <bool MAX> __device__ __forceinline__ double wave_total(double v)
 // Only the three sums that the decision needs are reduced, on the vector unit, and nothing waits
 // twice: 40^3 double (six march steps a block) 19.2 -> 17.9 us a sweep, 256^3 float 2% faster.
 // Smem: shared memory with `int last` and `double red[NW][NPART]`; THREADS threads in NW waves.
-template <int THREADS, int NW, class Smem>
-__device__ __forceinline__ void finish_step(const double* part, int nb, Ctl* ctl, bool restore, Smem& sm)
+// records: of REC doubles, the three sums at E, F2 and POW.
+template <int THREADS, int NW, int REC, int E, int F2, int POW, class Smem>
+__device__ __forceinline__ void finish_step(const double* part, int nb, int records, Ctl* ctl, bool restore, Smem& sm)
 {
     const int tid = threadIdx.x;
     Ctl c{};
@@ -1147,11 +1247,11 @@ __device__ __forceinline__ void finish_step(const double* part, int nb, Ctl* ctl
     }
     // the flow sweep sums the whole energy density in slot P_E2 (slots P_E4, P_E0, P_E6 are zero)
     double e = 0.0, f2 = 0.0, pw = 0.0;
-    for (int b = tid; b < nb; b += THREADS) {
-        const double* p = part + (size_t)b * NPART;
-        const double x0 = __hip_atomic_load(p + P_E2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const double x1 = __hip_atomic_load(p + P_F2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const double x2 = __hip_atomic_load(p + P_POW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int b = tid; b < records; b += THREADS) {
+        const double* p = part + (size_t)b * REC;
+        const double x0 = __hip_atomic_load(p + E, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const double x1 = __hip_atomic_load(p + F2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const double x2 = __hip_atomic_load(p + POW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         e += x0;
         f2 = fmax(f2, x1);
         pw += x2;
@@ -1229,6 +1329,39 @@ __device__ __forceinline__ void block_sums(double e2, double f2, double pw, doub
     }
 }
 
+// The same for a block of a batched sweep: the records of its units, `stride` doubles apart, from
+// the waves' sums over the `before` units before the last and the threads' over the last.  Lane
+// 3 u + q of wave 0 publishes sum q of unit u.
+template <int NWS, class Smem>
+__device__ __forceinline__ void unit_sums(double e, double f2, double pw, double f2_scale, double pw_scale, int before,
+                                          double* record, int stride, Smem& sm)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (wave < NWS) {
+        wave_totals(e, pw);
+        f2 = wave_total<true>(f2);
+        if (lane == 0) {
+            sm.red[wave][U_E] = e;
+            sm.red[wave][U_F2] = f2;
+            sm.red[wave][U_POW] = pw;
+        }
+    }
+    __syncthreads();
+    static_assert(3 * MAX_UNITS <= 64, "one lane per sum");
+    const int u = threadIdx.x / 3, q = threadIdx.x - 3 * u;
+    if (u <= before) {
+        double sum = 0.0, most = 0.0;
+#pragma unroll
+        for (int w = 0; w < NWS; ++w) {
+            const double v = u < before ? sm.unit[u][w][q] : sm.red[w][q];
+            sum += v;
+            most = fmax(most, v);
+        }
+        __hip_atomic_store(record + (size_t)u * stride + q, q == U_E ? sum : q == U_F2 ? most * f2_scale : sum * pw_scale, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 // One block's share of one field: logical block b of nb blocks, which takes the items b,
 // b + nb, ... of the field's work.  Used by the single-field and the batched kernels
 // (FROM_TABLE: the arguments were read from the batch's job table).
@@ -1299,31 +1432,56 @@ __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, S
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tiles = a.tiles_y * a.tiles_z;
     const int x0 = a.olo[0], nx = a.ohi[0] - a.olo[0] + 1;
-    const int items = tiles * ((nx + a.xchunk - 1) / a.xchunk);
+    // a block of a batched sweep: its slab, its first unit and how many
+    const int slab = b / tiles, unit0 = FROM_TABLE ? slab * a.per_block : 0;
+    const int own = FROM_TABLE ? min(a.units - unit0, a.per_block) : 0;
+    if constexpr (FROM_TABLE) {  // (read after the march's first barrier)
+        if (tid < own) sm.unit_end[tid] = unit_start(unit0 + tid + 1, nx, a.units) - unit_start(unit0, nx, a.units);
+        if (tid < G::NWI) sm.units_ended[tid] = 0;
+    }
+    const auto segment = [&](int item) {
+        Segment s = item_segment(item, tiles, a.tiles_z, x0, nx, a.xchunk);
+        if constexpr (FROM_TABLE) {
+            s.xa = x0 + unit_start(unit0, nx, a.units);
+            s.xe = x0 + unit_start(unit0 + own, nx, a.units);
+        }
+        return s;
+    };
+    const int items = FROM_TABLE ? nb : tiles * ((nx + a.xchunk - 1) / a.xchunk);
 
-    double e2 = 0.0, e4 = 0.0, e0 = 0.0, e6 = 0.0, bsum = 0.0, f2 = 0.0, pw = 0.0;
+    double e2 = 0.0, e4 = 0.0, e0 = 0.0, e6 = 0.0, bsum = 0.0, f2 = 0.0, pw = 0.0;  // f2, pw: scaled
     if (wave < G::NWI) {
         Interior<T, G, MODE, FROM_TABLE, EXT, STREAM> it(sm, k, cm, tid);
         for (int item = b; item < items; item += nb) {
-            it.setup(item_segment(item, tiles, a.tiles_z, x0, nx, a.xchunk), a.zstart);
+            it.setup(segment(item), a.zstart);
             it.march();
         }
         e2 = it.pe2;
         e4 = it.pe4;
         e0 = it.pe0;
         bsum = it.pb_sum * k.dinv12h3;
-        f2 = (double)it.pf2 * k.dinvK2;
-        pw = it.pp * k.dinvK;
+        f2 = (double)it.pf2;
+        pw = it.pp;
         e6 = it.pe6;
     } else {
         Halo<T, G, FROM_TABLE, EXT> hl(sm, k, cm, tid - G::NWI * 64);
         for (int item = b; item < items; item += nb) {
-            hl.setup(item_segment(item, tiles, a.tiles_z, x0, nx, a.xchunk), a.zstart);
+            hl.setup(segment(item), a.zstart);
             hl.march();
         }
     }
-    block_sums<G::NWI, MODE == MODE_STEP>(e2, f2, pw, e4, e0, bsum, e6, a.partials + (size_t)b * NPART, sm);
-    if constexpr (MODE == MODE_STEP) finish_step<G::THREADS, G::NW>(a.partials, nb, a.ctl, cm.restore != RESTORE_NONE, sm);
+    if constexpr (FROM_TABLE) {
+        // the records of the block's units, in the order of the units and tiles of the field
+        unit_sums<G::NWI>(e2, f2, pw, k.dinvK2, k.dinvK, own - 1,
+                          a.partials + (size_t)(unit0 * tiles + b - slab * tiles) * UNIT_REC, tiles * UNIT_REC, sm);
+        finish_step<G::THREADS, G::NW, UNIT_REC, U_E, U_F2, U_POW>(a.partials, nb, tiles * a.units, a.ctl,
+                                                                   cm.restore != RESTORE_NONE, sm);
+    } else {
+        block_sums<G::NWI, MODE == MODE_STEP>(e2, f2 * k.dinvK2, pw * k.dinvK, e4, e0, bsum, e6, a.partials + (size_t)b * NPART, sm);
+        if constexpr (MODE == MODE_STEP)
+            finish_step<G::THREADS, G::NW, NPART, P_E2, P_F2, P_POW>(a.partials, nb, nb, a.ctl,
+                                                                     cm.restore != RESTORE_NONE, sm);
+    }
 }
 
 // Blocks are dispatched round-robin over the eight XCDs (block i to XCD i % 8).
@@ -1347,8 +1505,8 @@ __global__ __launch_bounds__(G::THREADS) void sweep_kernel(SweepArgs a)
 // Many fields in one launch: launch block p sweeps block slot[p].y of field slot[p].x
 // (no field when slot[p].x < 0: a padding block that ends at once).  The host lays the
 // slots out for the round-robin dispatch of blocks over the XCDs (block p runs on XCD
-// p mod 8); every field's blocks and partial sums are exactly those of a launch of that
-// field alone.
+// p mod 8); a field's sums are taken per unit of planes, in the order of the units and tiles, and do not
+// depend on how many units its blocks march through.
 template <typename T, class G, int EXT, int STREAM>
 __global__ __launch_bounds__(G::THREADS) void batch_sweep_kernel(const SweepArgs* __restrict__ jobs,
                                                                  const int2* __restrict__ slot,
