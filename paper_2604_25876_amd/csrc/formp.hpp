@@ -184,20 +184,28 @@ template <typename T, int MODE, bool EXT, int STREAM> struct FormP {
         return v;
     }
 
-    // Loads of a plane.  Each component's base is formed by the scalar unit at its use: the bases of
+    // The base of a component.  In double it is formed by the scalar unit at its use: the bases of
     // four arrays' components, kept over the march, did not fit the scalar registers and came back
-    // from vector registers lane by lane.
+    // from vector registers lane by lane.  The float kernel has two waves per SIMD to hide that and
+    // loses to the extra scalar work (40 steps on 151^3: 2.68 ms so, 2.54 with the bases kept; 256^3
+    // 11.2 and 10.8; double 151^3 the other way, 10.5 ms kept and 9.85 formed, 50 steps).
+    template <typename P> __device__ __forceinline__ P comp(const P (&array)[4], int A) const
+    {
+        if constexpr (sizeof(T) == 8) return cm.comp(array[0], A);
+        else return array[A];
+    }
+    // loads of a plane
     __device__ __forceinline__ void load(unsigned o, int x, T (&dst)[4]) const
     {
         const unsigned base = (unsigned)clampi(x, 0, cm.n0 - 1) * cm.plane_b;
 #pragma unroll
-        for (int A = 0; A < 4; ++A) dst[A] = ldb(cm.comp(cm.pin[0], A), base + o);
+        for (int A = 0; A < 4; ++A) dst[A] = ldb(comp(cm.pin, A), base + o);
     }
     __device__ __forceinline__ void load_vel(int x)
     {
         const unsigned base = (unsigned)clampi(x, 0, cm.n0 - 1) * cm.plane_b;
 #pragma unroll
-        for (int A = 0; A < 4; ++A) vnxt[A] = ld_once<STREAM>((gptr<const T>)cm.comp(cm.vel[0], A), base + off);
+        for (int A = 0; A < 4; ++A) vnxt[A] = ld_once<STREAM>((gptr<const T>)comp(cm.vel, A), base + off);
     }
 
     // step s of the march: stage plane s, push D_x of its D_y phi and D_z phi, finish plane s-2
@@ -368,7 +376,7 @@ template <typename T, int MODE, bool EXT, int STREAM> struct FormP {
             if (cm.restore) {
 #pragma unroll
                 for (int A = 0; A < 4; ++A)
-                    st_once<STREAM>(cm.comp(cm.vel[0], A), base, cm.restore == RESTORE_ZERO ? T(0) : fmaT(-k.dtK, f[A], vcur[A]));
+                    st_once<STREAM>(comp(cm.vel, A), base, cm.restore == RESTORE_ZERO ? T(0) : fmaT(-k.dtK, f[A], vcur[A]));
                 return;
             }
             T v[4], q[4], pn[4];
@@ -394,13 +402,13 @@ template <typename T, int MODE, bool EXT, int STREAM> struct FormP {
             }
 #pragma unroll
             for (int A = 0; A < 4; ++A) {
-                st_once<STREAM>(cm.comp(cm.pout[0], A), base, pn[A]);
-                st_once<STREAM>(cm.comp(cm.vel[0], A), base, v[A]);
+                st_once<STREAM>(comp(cm.pout, A), base, pn[A]);
+                st_once<STREAM>(comp(cm.vel, A), base, v[A]);
             }
         } else {
             if (cm.has_grad) {
 #pragma unroll
-                for (int A = 0; A < 4; ++A) st_once<STREAM>(cm.comp(cm.gout[0], A), base, (cm.projected ? -f[A] : g[A]) * k.invK);
+                for (int A = 0; A < 4; ++A) st_once<STREAM>(comp(cm.gout, A), base, (cm.projected ? -f[A] : g[A]) * k.invK);
             }
         }
     }
