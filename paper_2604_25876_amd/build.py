@@ -12,7 +12,7 @@ PKG = Path(__file__).resolve().parent
 ROOT = PKG.parent
 SOURCES = [PKG / "csrc" / n for n in ("skyr.hip", "kernels_step_f64.hip", "kernels_step_f32.hip",
                                       "kernels_batch_f64.hip", "kernels_batch_f32.hip", "kernels_grad.hip")]
-DEPS = SOURCES + [PKG / "csrc" / n for n in ("sweep.hpp", "shapes.hpp", "kernels.hpp", "moments.hpp", "formp.hpp")] + \
+DEPS = SOURCES + [PKG / "csrc" / n for n in ("sweep.hpp", "cut.hpp", "shapes.hpp", "kernels.hpp", "moments.hpp", "formp.hpp")] + \
     [ROOT / "include" / "skyr.h"]
 LIB = PKG / "libskyr.so"
 

@@ -282,7 +282,7 @@ static Launch batch_default_launch(const skyr_lattice* lat, skyr_precision prec,
 {
     Launch L = plan_with(lat, prec, v, xc);
     const int nx = lat->n[0] - 4;
-    L.units = std::min(nx, 2 * ((nx + 2 * kMinChunk - 1) / (2 * kMinChunk)));
+    L.units = default_units(nx, kMinChunk);
     L.per_block = (L.units + L.slabs - 1) / L.slabs;
     L.free_slabs = true;
     return L;
@@ -305,9 +305,7 @@ static Launch plan_batch(const skyr_lattice* lat, skyr_precision prec)
 // units allow.
 static void cut_slabs(Launch& L, int nx, int cap)
 {
-    const int most = std::max(1, std::min(MAX_UNITS, cap * L.units / nx));
-    L.slabs = (L.units + most - 1) / most;
-    L.per_block = (L.units + L.slabs - 1) / L.slabs;
+    L.per_block = slab_units(nx, L.units, cap);
     L.slabs = (L.units + L.per_block - 1) / L.per_block;
 }
 
@@ -2011,11 +2009,7 @@ static skyr_status upload_ints(const std::vector<int>& v, int*& d, int& cap)
 }
 
 // planes of slab `slab` of a field in a batch
-static int slab_planes(const Launch& L, int nx, int slab)
-{
-    const int first = slab * L.per_block, end = std::min(L.units, first + L.per_block);
-    return end * nx / L.units - first * nx / L.units;
-}
+static int slab_planes(const Launch& L, int nx, int slab) { return slab_planes(slab, L.per_block, nx, L.units); }
 
 // Sweep time of block `blk` of a job, in the units of a shape's cost factor: the planes
 // of its item (with what a block pays on top) times the item's output columns.

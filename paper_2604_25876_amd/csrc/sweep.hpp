@@ -41,6 +41,7 @@
 #include <stdint.h>
 
 #include "../../include/skyr.h"
+#include "cut.hpp"
 
 #include <type_traits>
 
@@ -319,7 +320,6 @@ template <int NWI_, int NWH_, int HPT_, int OZ_> struct Geo {
 // A batched sweep keeps a field's sums per unit of planes; records of energy density, largest
 // |F|^2 and power, at most MAX_UNITS of them from one block.
 enum : int { U_E = 0, U_F2 = 1, U_POW = 2, UNIT_REC = 4 };
-constexpr int MAX_UNITS = 16;
 
 template <typename T, class G> struct SweepSmem {
     SitePlane<T, G::PPLANE> phi[2];     // [plane parity]
@@ -472,9 +472,6 @@ __device__ __forceinline__ Segment item_segment(int item, int tiles, int tiles_z
     s.xe = x0 + min(nx, (slab + 1) * xchunk);
     return s;
 }
-
-// first plane of unit k of a field's nx planes in `units` units of the same length (but one)
-__device__ __forceinline__ int unit_start(int k, int nx, int units) { return k * nx / units; }
 
 // Fields, flags and sums shared by the two roles.
 template <typename T, bool FROM_TABLE> struct SweepCommon {
