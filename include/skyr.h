@@ -349,8 +349,9 @@ typedef struct {
 SKYR_API int64_t skyr_block_sites(const skyr_block* blk);
 SKYR_API int64_t skyr_block_shell_sites(const skyr_block* blk);
 
-/* Bytes of device workspace skyr_block_sweep needs (0 on invalid arguments); 256-byte
- * aligned, not shared by calls that overlap in time. */
+/* Bytes of device workspace skyr_block_sweep needs (0 on invalid arguments), whatever tile
+ * is set or tuned before or after; 256-byte aligned, not shared by calls that overlap in
+ * time. */
 SKYR_API size_t skyr_block_workspace_bytes(const skyr_block* blk, skyr_precision prec);
 
 /* The block's share of the sums of one sweep, over its own sites in I: added over all

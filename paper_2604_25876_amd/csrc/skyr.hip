@@ -341,6 +341,9 @@ constexpr size_t CTL_BYTES = 256;
 constexpr size_t OBS_BYTES = 512;
 constexpr size_t MOM_CENTRE_OFFSET = 64;
 constexpr size_t MOM_OUT_OFFSET = 128;
+static_assert((size_t)kMaxBlocks * NPART <= (size_t)MOM_MAX_BLOCKS * MOM_NACC, "records of a default launch in every workspace");
+static_assert(CTL_BYTES + OBS_BYTES + (size_t)kMaxBlocks * NPART * sizeof(double) <= SKYR_NOALLOC_SCRATCH_BYTES,
+              "records of a default launch in the fixed scratch");
 static_assert(MOM_OUT_OFFSET + MOM_OUT_DOUBLES * sizeof(double) <= OBS_BYTES, "moment result must fit");
 static_assert(sizeof(skyr_moment_obs) == MOM_OUT_DOUBLES * sizeof(double), "moment record layout");
 
@@ -1420,9 +1423,17 @@ static Launch plan_block(const BlockGeo& g, skyr_precision prec)
     return L;
 }
 
+// room for every launch that plan_block may choose, now or after a change of the region's tile: the
+// default's, of at most kMaxBlocks blocks, and every shape with slabs of kMinChunk planes or more
 static size_t block_work_bytes(const BlockGeo& g, skyr_precision prec)
 {
-    return CTL_BYTES + OBS_BYTES + (size_t)plan_block(g, prec).blocks() * NPART * sizeof(double);
+    long long oe[3], most = kMaxBlocks;
+    for (int d = 0; d < 3; ++d) oe[d] = std::max(1, g.ohi[d] - g.olo[d] + 1);
+    for (int v = 0; v < shape_count(prec); ++v) {
+        const int oy = shape_of(prec, v).oy(), oz = shape_of(prec, v).oz();
+        most = std::max(most, (oe[0] + kMinChunk - 1) / kMinChunk * ((oe[1] + oy - 1) / oy) * ((oe[2] + oz - 1) / oz));
+    }
+    return CTL_BYTES + OBS_BYTES + (size_t)most * NPART * sizeof(double);
 }
 
 // rank of padded site (x, y, z) among the shell sites (row-major order, own box left out)
