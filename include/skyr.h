@@ -462,10 +462,14 @@ SKYR_API skyr_status skyr_moments(const skyr_lattice* lat, skyr_precision prec, 
  * load asks, few fields into short slabs and many into long ones, but their
  * sums are kept per unit of at most 16 planes in an order of their own, so a
  * field's result does not depend on the other fields in the batch (it is the
- * same bytes).  It equals that of skyr_anf_step up to the order of the sums.  A batch object owns only its job table,
- * control blocks and graph; field, velocity and workspace memory stay with
- * the caller and must stay valid while the field is in the batch.  A batch is
- * used by one thread at a time.
+ * same bytes).  It equals that of skyr_anf_step up to the order of the sums.  A
+ * field on a batch tile that was set to another choice than the default runs in
+ * the blocks of that tile, with their sums, and its result is, byte for byte,
+ * that of skyr_anf_step when skyr_set_tile gives the lattice the same tile (other
+ * than that one's default).  A batch object owns only its job table, control
+ * blocks and graph; field, velocity and workspace memory stay with the caller
+ * and must stay valid while the field is in the batch.  A batch is used by one
+ * thread at a time.
  *   skyr_batch_create  max_jobs slots; work is enqueued on `stream`
  *   skyr_batch_add     a fresh flow (state as after skyr_anf_state_init, zero
  *                      velocity); runs until max|F| < flow->tol or

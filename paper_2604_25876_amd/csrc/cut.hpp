@@ -10,15 +10,19 @@ namespace skyr {
 // records of a block: the most units that one slab may hold
 constexpr int MAX_UNITS = 16;
 
-// First plane of unit k of a field's nx planes in `units` units of the same length (but one).  The
-// product is formed in 64 bits: k reaches nx / 16 or so, and k nx passes 2^31 from 185,352 planes on.
-constexpr int unit_start(int k, int nx, int units) { return (int)((long long)k * nx / units); }
+// First plane of unit k of a field's nx planes in `units` units: of `len` planes (the last one of
+// those that are left), or all of the same length (but one) where len is 0.  The products are formed
+// in 64 bits: k reaches nx / 16 or so, and k nx passes 2^31 from 185,352 planes on.
+constexpr int unit_start(int k, int nx, int units, int len)
+{
+    return len > 0 ? (int)std::min<long long>(nx, (long long)k * len) : (int)((long long)k * nx / units);
+}
 
 // planes of slab `slab`, of per_block units
-constexpr int slab_planes(int slab, int per_block, int nx, int units)
+constexpr int slab_planes(int slab, int per_block, int nx, int units, int len)
 {
     const int first = slab * per_block, end = std::min(units, first + per_block);
-    return unit_start(end, nx, units) - unit_start(first, nx, units);
+    return unit_start(end, nx, units, len) - unit_start(first, nx, units, len);
 }
 
 // units of a field on its default batch tile: an even number, of at most `planes` planes each

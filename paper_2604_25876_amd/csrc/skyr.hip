@@ -88,9 +88,10 @@ struct Launch {
     Shape shape;
     int xchunk;  // planes per slab
     // in batches: the units of planes that partial sums are kept for, and units per slab; a batch
-    // chooses per_block where free_slabs
+    // chooses per_block where free_slabs (else a unit is a slab of xchunk planes)
     int units, per_block;
     bool free_slabs;
+    int unit_len() const { return free_slabs ? 0 : xchunk; }
     int tiles_z, tiles_y, zstart, slabs;
     int blocks() const { return tiles_z * tiles_y * slabs; }
     int threads() const { return shape.threads(); }
@@ -637,6 +638,7 @@ static SweepArgs make_args(const skyr_lattice* lat, const Launch& L, const skyr_
     a.xchunk = L.xchunk;
     a.units = L.units;
     a.per_block = L.per_block;
+    a.unit_len = L.unit_len();
     a.h = lat->h;
     a.m = model->m;
     a.m_y = model->m_y;
@@ -2020,7 +2022,7 @@ static skyr_status upload_ints(const std::vector<int>& v, int*& d, int& cap)
 }
 
 // planes of slab `slab` of a field in a batch
-static int slab_planes(const Launch& L, int nx, int slab) { return slab_planes(slab, L.per_block, nx, L.units); }
+static int slab_planes(const Launch& L, int nx, int slab) { return slab_planes(slab, L.per_block, nx, L.units, L.unit_len()); }
 
 // Sweep time of block `blk` of a job, in the units of a shape's cost factor: the planes
 // of its item (with what a block pays on top) times the item's output columns.

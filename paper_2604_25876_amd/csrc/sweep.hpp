@@ -120,6 +120,7 @@ struct SweepArgs {
     int zstart;            // z of the first tile's first column (at most olo[2]; below it for line-aligned tiles)
     int xchunk;            // planes per slab (the work order's outer unit)
     int units, per_block;  // batched sweeps (instead of xchunk): units of planes, and units of one block
+    int unit_len;          // planes of a unit (a tile that was set: one slab each), 0 for units of one length
     int projected;     // MODE_GRAD: write g - (g.phi) phi instead of g
     int baryon;        // accumulate the baryon density
     double h, dt;
@@ -318,7 +319,8 @@ template <int NWI_, int NWH_, int HPT_, int OZ_> struct Geo {
 };
 
 // A batched sweep keeps a field's sums per unit of planes; records of energy density, largest
-// |F|^2 and power, at most MAX_UNITS of them from one block.
+// |F|^2 and power, at most MAX_UNITS of them from one block.  On a tile that was set a unit is a slab,
+// and the sums are formed in the order of the single-field sweep: its records, bit for bit.
 enum : int { U_E = 0, U_F2 = 1, U_POW = 2, UNIT_REC = 4 };
 
 template <typename T, class G> struct SweepSmem {
@@ -389,47 +391,42 @@ template <int CTRL> __device__ __forceinline__ double dpp_f64(double v)
     const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
-// The sum (maximum) of v over the wave, in every lane, in a fixed order: lanes 1 and 2 away, then
-// (the sums of all lanes of a quad being equal) the mirrored lanes of 8 and 16, then the lanes 16
-// and 32 away: a swap of two copies' halves leaves one half's sum in one copy and the other's in
-// the other.
-template <bool MAX> __device__ __forceinline__ double wave_total(double v)
+// The stages of a wave's sums below: lanes 32 and 16 away (a swap of two copies' halves, or of their
+// rows, leaves one's in one copy and the other's in the other), then 8, 4, 2 and 1 away within a row
+// of 16: the order of a butterfly, the same in wave_total and wave_totals, so that a sum does not
+// depend on which of them formed it.
+template <bool MAX, class Swap> __device__ __forceinline__ double wave_halves(double a, double b, Swap swap)
+{
+    const unsigned long long ua = __builtin_bit_cast(unsigned long long, a), ub = __builtin_bit_cast(unsigned long long, b);
+    const auto lo = swap((unsigned)ua, (unsigned)ub), hi = swap((unsigned)(ua >> 32), (unsigned)(ub >> 32));
+    const double x = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
+    const double y = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+    return MAX ? fmax(x, y) : x + y;
+}
+// the stages below 32 lanes
+template <bool MAX> __device__ __forceinline__ double wave_rows(double v)
 {
     const auto add = [](double a, double b) { return MAX ? fmax(a, b) : a + b; };
-    v = add(v, dpp_f64<0xb1>(v));   // quad lanes 1, 0, 3, 2
+    v = wave_halves<MAX>(v, v, [](unsigned x, unsigned y) { return __builtin_amdgcn_permlane16_swap(x, y, false, false); });
+    v = add(v, dpp_f64<0x128>(v));  // turned by 8 lanes of 16
+    v = add(v, dpp_f64<0x124>(v));  // by 4 (lanes 8 apart being equal, 4 away)
     v = add(v, dpp_f64<0x4e>(v));   // quad lanes 2, 3, 0, 1
-    v = add(v, dpp_f64<0x141>(v));  // mirrored in 8 lanes
-    v = add(v, dpp_f64<0x140>(v));  // mirrored in 16 lanes
-    const auto halves = [&](auto swap) {
-        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-        const auto lo = swap((unsigned)u), hi = swap((unsigned)(u >> 32));
-        const double x = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
-        const double y = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
-        return add(x, y);
-    };
-    v = halves([](unsigned u) { return __builtin_amdgcn_permlane16_swap(u, u, false, false); });
-    v = halves([](unsigned u) { return __builtin_amdgcn_permlane32_swap(u, u, false, false); });
+    v = add(v, dpp_f64<0xb1>(v));   // quad lanes 1, 0, 3, 2
     return v;
+}
+// the sum (maximum) of v over the wave, in every lane
+template <bool MAX> __device__ __forceinline__ double wave_total(double v)
+{
+    return wave_rows<MAX>(
+        wave_halves<MAX>(v, v, [](unsigned x, unsigned y) { return __builtin_amdgcn_permlane32_swap(x, y, false, false); }));
 }
 
 // a and b summed over the wave: a in lanes 0 .. 31, b in lanes 32 .. 63 from the first stage on
 // (two sums for little more than one); every lane of the lower half ends with a's, all with b's total
 __device__ __forceinline__ void wave_totals(double& a, double& b)
 {
-    const unsigned long long ua = __builtin_bit_cast(unsigned long long, a), ub = __builtin_bit_cast(unsigned long long, b);
-    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
-    double v = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
-               __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
-    v += dpp_f64<0xb1>(v);
-    v += dpp_f64<0x4e>(v);
-    v += dpp_f64<0x141>(v);
-    v += dpp_f64<0x140>(v);
-    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)u, (unsigned)u, false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
-    v = __builtin_bit_cast(double, ((unsigned long long)h[0] << 32) | l[0]) +
-        __builtin_bit_cast(double, ((unsigned long long)h[1] << 32) | l[1]);
+    const double v = wave_rows<false>(
+        wave_halves<false>(a, b, [](unsigned x, unsigned y) { return __builtin_amdgcn_permlane32_swap(x, y, false, false); }));
     const unsigned long long w = __builtin_bit_cast(unsigned long long, v);
     a = v;
     b = __builtin_bit_cast(double, ((unsigned long long)__builtin_amdgcn_readlane((unsigned)(w >> 32), 32) << 32) |
@@ -878,19 +875,19 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT, int STREAM> s
             asm volatile("" : "+s"(last));
             if (st >= last - xa + 4) return true;
             const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-            const int k = __builtin_amdgcn_readfirstlane(sm.units_ended[wave]);
-            double e = pe2, p = pp;
+            const int u = __builtin_amdgcn_readfirstlane(sm.units_ended[wave]);
+            double e = pe2, p = pp * k.dinvK;
             wave_totals(e, p);
             const T f = wave_most(pf2);
             if ((threadIdx.x & 63) == 0) {
-                sm.unit[k][wave][U_E] = e;
-                sm.unit[k][wave][U_F2] = (double)f;
-                sm.unit[k][wave][U_POW] = p;
-                sm.units_ended[wave] = k + 1;
+                sm.unit[u][wave][U_E] = e;
+                sm.unit[u][wave][U_F2] = (double)f * k.dinvK2;
+                sm.unit[u][wave][U_POW] = p;
+                sm.units_ended[wave] = u + 1;
             }
             pe2 = pp = 0.0;
             pf2 = T(0);
-            ev = next_event(k + 1);
+            ev = next_event(u + 1);
             return false;
         } else {
             return true;
@@ -1330,8 +1327,8 @@ __device__ __forceinline__ void block_sums(double e2, double f2, double pw, doub
 // the waves' sums over the `before` units before the last and the threads' over the last.  Lane
 // 3 u + q of wave 0 publishes sum q of unit u.
 template <int NWS, class Smem>
-__device__ __forceinline__ void unit_sums(double e, double f2, double pw, double f2_scale, double pw_scale, int before,
-                                          double* record, int stride, Smem& sm)
+__device__ __forceinline__ void unit_sums(double e, double f2, double pw, int before, double* record, int stride,
+                                          Smem& sm)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (wave < NWS) {
@@ -1354,8 +1351,7 @@ __device__ __forceinline__ void unit_sums(double e, double f2, double pw, double
             sum += v;
             most = fmax(most, v);
         }
-        __hip_atomic_store(record + (size_t)u * stride + q, q == U_E ? sum : q == U_F2 ? most * f2_scale : sum * pw_scale, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(record + (size_t)u * stride + q, q == U_F2 ? most : sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -1433,14 +1429,15 @@ __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, S
     const int slab = b / tiles, unit0 = FROM_TABLE ? slab * a.per_block : 0;
     const int own = FROM_TABLE ? min(a.units - unit0, a.per_block) : 0;
     if constexpr (FROM_TABLE) {  // (read after the march's first barrier)
-        if (tid < own) sm.unit_end[tid] = unit_start(unit0 + tid + 1, nx, a.units) - unit_start(unit0, nx, a.units);
+        if (tid < own)
+            sm.unit_end[tid] = unit_start(unit0 + tid + 1, nx, a.units, a.unit_len) - unit_start(unit0, nx, a.units, a.unit_len);
         if (tid < G::NWI) sm.units_ended[tid] = 0;
     }
     const auto segment = [&](int item) {
         Segment s = item_segment(item, tiles, a.tiles_z, x0, nx, a.xchunk);
         if constexpr (FROM_TABLE) {
-            s.xa = x0 + unit_start(unit0, nx, a.units);
-            s.xe = x0 + unit_start(unit0 + own, nx, a.units);
+            s.xa = x0 + unit_start(unit0, nx, a.units, a.unit_len);
+            s.xe = x0 + unit_start(unit0 + own, nx, a.units, a.unit_len);
         }
         return s;
     };
@@ -1469,7 +1466,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, S
     }
     if constexpr (FROM_TABLE) {
         // the records of the block's units, in the order of the units and tiles of the field
-        unit_sums<G::NWI>(e2, f2, pw, k.dinvK2, k.dinvK, own - 1,
+        unit_sums<G::NWI>(e2, f2 * k.dinvK2, pw * k.dinvK, own - 1,
                           a.partials + (size_t)(unit0 * tiles + b - slab * tiles) * UNIT_REC, tiles * UNIT_REC, sm);
         finish_step<G::THREADS, G::NW, UNIT_REC, U_E, U_F2, U_POW>(a.partials, nb, tiles * a.units, a.ctl,
                                                                    cm.restore != RESTORE_NONE, sm);

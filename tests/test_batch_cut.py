@@ -14,10 +14,11 @@ DRIVER = """
 #include "cut.hpp"
 using namespace skyr;
 extern "C" {
-int u_start(int k, int nx, int units) { return unit_start(k, nx, units); }
+int u_start(int k, int nx, int units) { return unit_start(k, nx, units, 0); }
+int u_start_len(int k, int nx, int units, int len) { return unit_start(k, nx, units, len); }
 int u_default(int nx) { return default_units(nx, 16); }
 int u_slab(int nx, int units, int cap) { return slab_units(nx, units, cap); }
-int u_planes(int slab, int per, int nx, int units) { return slab_planes(slab, per, nx, units); }
+int u_planes(int slab, int per, int nx, int units) { return slab_planes(slab, per, nx, units, 0); }
 }
 """
 
@@ -54,3 +55,12 @@ def test_units_and_slabs(cut, nx):
             planes = cut.u_planes(s, per, nx, units)
             assert planes == end * nx // units - first * nx // units
             assert 1 <= planes <= max(cap, 16)
+
+
+# a tile that was set: slabs of the length that was set, the last one of what is left
+@pytest.mark.parametrize("nx", [1, 15, 16, 17, 124, 200000, 2 ** 29 // 25 - 4])
+@pytest.mark.parametrize("length", [16, 100, 1000, 2 ** 31 - 1])
+def test_units_of_a_set_length(cut, nx, length):
+    units = -(-nx // length)
+    for k in {0, 1, units // 2, units - 1, units} & set(range(units + 1)):
+        assert cut.u_start_len(k, nx, units, length) == min(nx, k * length)
