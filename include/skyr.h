@@ -527,13 +527,16 @@ SKYR_API skyr_status skyr_batch_destroy(skyr_batch* b);
  * launch with another shape and shorter slabs where that is faster (a small lattice
  * on more of the device): field values do not depend on either, only the order of
  * the sums does.  A tile set to the default choice is the default; any other is used
- * as it was set.  Fields in batches have a
+ * as it was set.  (Slabs are of at least 16 planes; on a lattice of fewer the default
+ * choice is accepted with its own length, and with 16 in its place is the default too.)
+ * Fields in batches have a
  * tile setting of their own (skyr_set_batch_tile, skyr_batch_autotune) whose
  * default is the precision's first shape (variant 0: the fields of one
  * precision then share one launch per sweep slot) with x split evenly into the
  * fewest slabs of at most 64 planes; as with a single field that default is what
  * is reported, and the batch launches the slabs that suit its load (see above).
- * A batch tile set to another choice is used as it was set.  The getters report the setting in force, the default included. */
+ * A batch tile set to another choice is used as it was set.  The getters report the
+ * setting in force, the default included, and what they report can be set again. */
 SKYR_API int32_t skyr_tile_variants(skyr_precision prec);
 SKYR_API skyr_status skyr_tile_variant_info(skyr_precision prec, int32_t variant, int32_t info[3]);
 SKYR_API skyr_status skyr_set_tile(const skyr_lattice* lat, skyr_precision prec, int32_t variant, int32_t xchunk);

@@ -231,6 +231,13 @@ static Launch default_launch(const skyr_lattice* lat, skyr_precision prec, int v
     return best;
 }
 
+// Whether a tile that was set is the default choice: the pair itself, or, where a lattice has fewer
+// than kMinChunk planes, the pair with the shortest slab that is otherwise accepted (the same cut).
+static bool is_default_choice(const std::pair<int, int>& set, int v, int xc)
+{
+    return set.first == v && (set.second == xc || set.second == std::max(kMinChunk, xc));
+}
+
 // the launch of a lattice: its own tile where one was set or tuned, else the default's
 static Launch plan(const skyr_lattice* lat, skyr_precision prec)
 {
@@ -239,7 +246,7 @@ static Launch plan(const skyr_lattice* lat, skyr_precision prec)
     {
         std::lock_guard<std::mutex> g(g_tile_mu);
         auto it = g_tiles.find(TileKey{lat->n[0], lat->n[1], lat->n[2], (int)prec});
-        if (it != g_tiles.end() && it->second != std::make_pair(v, xc))
+        if (it != g_tiles.end() && !is_default_choice(it->second, v, xc))
             return plan_with(lat, prec, it->second.first, it->second.second);
     }
     return default_launch(lat, prec, v, xc);
@@ -289,6 +296,19 @@ static Launch batch_default_launch(const skyr_lattice* lat, skyr_precision prec,
     return L;
 }
 
+// the batch tile in force, as its getter reports it
+static std::pair<int, int> batch_tile_in_force(const skyr_lattice* lat, skyr_precision prec)
+{
+    {
+        std::lock_guard<std::mutex> g(g_tile_mu);
+        auto it = g_batch_tiles.find(TileKey{lat->n[0], lat->n[1], lat->n[2], (int)prec});
+        if (it != g_batch_tiles.end()) return it->second;
+    }
+    int v = 0, xc = 0;
+    batch_default_tile(lat, prec, v, xc);
+    return {v, xc};
+}
+
 static Launch plan_batch(const skyr_lattice* lat, skyr_precision prec)
 {
     int v = 0, xc = 0;
@@ -296,7 +316,7 @@ static Launch plan_batch(const skyr_lattice* lat, skyr_precision prec)
     {
         std::lock_guard<std::mutex> g(g_tile_mu);
         auto it = g_batch_tiles.find(TileKey{lat->n[0], lat->n[1], lat->n[2], (int)prec});
-        if (it != g_batch_tiles.end() && it->second != std::make_pair(v, xc))
+        if (it != g_batch_tiles.end() && !is_default_choice(it->second, v, xc))
             return plan_with(lat, prec, it->second.first, it->second.second);
     }
     return batch_default_launch(lat, prec, v, xc);
@@ -1762,7 +1782,10 @@ skyr_status skyr_set_tile(const skyr_lattice* lat, skyr_precision prec, int32_t 
     skyr_status st = check_lattice(lat, prec);
     if (st != SKYR_OK) return st;
     if (variant < 0 || variant >= shape_count(prec)) return fail(SKYR_E_INVAL, "no such tile variant");
-    if (xchunk < kMinChunk) return fail(SKYR_E_INVAL, "slabs must have at least 16 planes");
+    int dv = 0, dx = 0;
+    default_tile(lat, prec, dv, dx);
+    if (xchunk < kMinChunk && !is_default_choice({variant, xchunk}, dv, dx))
+        return fail(SKYR_E_INVAL, "slabs must have at least 16 planes");
     std::lock_guard<std::mutex> g(g_tile_mu);
     g_tiles[TileKey{lat->n[0], lat->n[1], lat->n[2], (int)prec}] = {variant, xchunk};
     return SKYR_OK;
@@ -1783,7 +1806,10 @@ skyr_status skyr_set_batch_tile(const skyr_lattice* lat, skyr_precision prec, in
     skyr_status st = check_lattice(lat, prec);
     if (st != SKYR_OK) return st;
     if (variant < 0 || variant >= shape_count(prec)) return fail(SKYR_E_INVAL, "no such tile variant");
-    if (xchunk < kMinChunk) return fail(SKYR_E_INVAL, "slabs must have at least 16 planes");
+    int dv = 0, dx = 0;
+    batch_default_tile(lat, prec, dv, dx);
+    if (xchunk < kMinChunk && !is_default_choice({variant, xchunk}, dv, dx))
+        return fail(SKYR_E_INVAL, "slabs must have at least 16 planes");
     std::lock_guard<std::mutex> g(g_tile_mu);
     g_batch_tiles[TileKey{lat->n[0], lat->n[1], lat->n[2], (int)prec}] = {variant, xchunk};
     return SKYR_OK;
@@ -1793,9 +1819,9 @@ skyr_status skyr_get_batch_tile(const skyr_lattice* lat, skyr_precision prec, in
 {
     skyr_status st = check_lattice(lat, prec);
     if (st != SKYR_OK) return st;
-    const Launch L = plan_batch(lat, prec);
-    if (variant) *variant = L.variant;
-    if (xchunk) *xchunk = L.xchunk;
+    const std::pair<int, int> t = batch_tile_in_force(lat, prec);
+    if (variant) *variant = t.first;
+    if (xchunk) *xchunk = t.second;
     return SKYR_OK;
 }
 
