@@ -59,7 +59,7 @@ def build_sanitized(out: Path, verbose: bool = False) -> Path:
            "-Xarch_host", "-fsanitize=address",
            "-Xarch_host", "-fsanitize=undefined",
            "-Xarch_host", "-fno-sanitize-recover=undefined",
-           "-DSKYR_SHAPES_F64(X)=X(4, 4, 1, 16, 1, 1.0)", "-DSKYR_SHAPES_F32(X)=X(8, 4, 1, 32, 1, 1.0)",
+           "-DSKYR_SHAPES_F64(X)=X(4, 4, 1, 16, 1, 1.0, 1.6, 1.6)", "-DSKYR_SHAPES_F32(X)=X(8, 4, 1, 32, 1, 1.0, 1.5, 1.5)",
            "-I", str(ROOT / "include"), "-o", str(tmp), *map(str, SOURCES)]
     if verbose:
         print(" ".join(cmd), flush=True)

@@ -21,7 +21,7 @@ template <typename T, class G> static const void* of_ext(int ext, int stream, in
 template <> const void* batch_kernel_of<float>(int variant, int ext, int stream, int& threads)
 {
     int v = 0;
-#define SKYR_CASE(a, b, c, d, e, f) \
+#define SKYR_CASE(a, b, c, d, ...) \
     if (variant == v) return of_ext<float, Geo<a, b, c, d>>(ext, stream, threads); \
     ++v;
     SKYR_SHAPES_F32(SKYR_CASE)

@@ -18,14 +18,14 @@ const void* grad_kernel(skyr_precision prec, int variant, int ext, int& threads)
     const int stream = STREAM_ALL;
     if (prec == SKYR_F64) {
         int v = 0;
-#define SKYR_CASE(a, b, c, d, e, f) \
+#define SKYR_CASE(a, b, c, d, ...) \
     if (variant == v) return grad_of<double, Geo<a, b, c, d>>(ext, stream, threads); \
     ++v;
         SKYR_SHAPES_F64(SKYR_CASE)
 #undef SKYR_CASE
     } else {
         int v = 0;
-#define SKYR_CASE(a, b, c, d, e, f) \
+#define SKYR_CASE(a, b, c, d, ...) \
     if (variant == v) return grad_of<float, Geo<a, b, c, d>>(ext, stream, threads); \
     ++v;
         SKYR_SHAPES_F32(SKYR_CASE)

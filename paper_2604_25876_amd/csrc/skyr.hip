@@ -52,26 +52,11 @@ static skyr_status fail(skyr_status s, const std::string& msg)
 // ------------------------------------------------------------ tile choice
 // A tile shape is (interior waves, halo waves, halo positions per halo lane,
 // output columns); a tile has interior waves x 64 / columns rows.  A few shapes
-// are compiled per precision.  x is cut into slabs of `xchunk` planes; a launch
+// are compiled per precision (shapes.hpp).  x is cut into slabs of `xchunk` planes; a launch
 // has one block per (slab, tile) item, so that the blocks of neighbouring tiles
 // march through the same planes together and share their halo lines in L2.  The
 // choice for a (lattice, precision) pair is a process-wide setting
-// (skyr_set_tile / skyr_autotune).  The last entry of a shape is the relative time of one
-// output site and plane of an item in a full round of the chip (measured at 256^3; a shape
-// that puts two blocks on a CU takes about twice as long per item), for the default choice.
-struct Shape {
-    int nwi, nwh, hpt, cols;
-    int per_cu;   // blocks resident on one CU (LDS and registers)
-    double cost;  // relative time per output site and plane
-    int threads() const { return (nwi + nwh) * 64; }
-    int oy() const { return nwi * 64 / cols; }
-    int oz() const { return cols; }
-};
-
-#include "shapes.hpp"
-#define SKYR_SHAPE_ENTRY(a, b, c, d, e, f) Shape{a, b, c, d, e, f},
-static const Shape kShapesF64[] = {SKYR_SHAPES_F64(SKYR_SHAPE_ENTRY)};
-static const Shape kShapesF32[] = {SKYR_SHAPES_F32(SKYR_SHAPE_ENTRY)};
+// (skyr_set_tile / skyr_autotune).
 constexpr int kMinChunk = 16;  // shortest slab (planes)
 constexpr int kMaxSlabs = 8;   // the default and the autotuner use 1 .. kMaxSlabs slabs
 constexpr int kCUs = 256;      // compute units of the device the launches are sized for
@@ -182,15 +167,12 @@ static void default_tile(const skyr_lattice* lat, skyr_precision prec, int& v_ou
 // kMinChunk) stays what skyr_get_tile reports; the launch may take another shape and shorter
 // slabs, since field values do not depend on either.  A block marches xc + 4 planes and pays for
 // about two more (its first loads, its sums); a launch of r rounds of the chip takes r (xc + 6)
-// times the time of a step of its shape, 15% more when r > 1.  With the step times below this picks
+// times the time of a step of its shape, 15% more when r > 1.  With the shapes' step times this picks
 // within 1.2% of the fastest of all (shape, slab length) pairs, measured on cubes of 40 .. 256
 // sites in both precisions: one round with as many slabs as it holds, where the lattice is small
 // enough.  40^3: 2-plane slabs, 108-162 blocks, 19-21 us a sweep against 42-43.5 with the default
 // tile's 18 blocks; 96^3: 31 / 39 us (float / double) against 44 / 47; 128^3 float 41 against 44;
 // 256^3 double on 8 x 32 tiles 451 against 478.
-constexpr double kStepF64[] = {1.6, 1.52, 2.2};  // microseconds a step, one block per CU
-constexpr double kStepF32[] = {1.5, 1.3, 2.0};
-constexpr double kStepF32Pair = 2.2;  // the second float shape with two blocks on a CU
 // no launch has more blocks than every workspace (and the fixed scratch) has records for
 constexpr int kMaxBlocks = 4084;
 
@@ -200,8 +182,7 @@ static double launch_cost(skyr_precision prec, int v, int xc, long long blocks)
     const bool pair = sh.per_cu > 1 && blocks > kCUs;
     const long long per_round = (long long)kCUs * (pair ? sh.per_cu : 1);
     const long long rounds = (blocks + per_round - 1) / per_round;
-    const double step = prec == SKYR_F64 ? kStepF64[v] : pair ? kStepF32Pair : kStepF32[v];
-    return (double)rounds * (rounds > 1 ? kMultiRoundCost : 1.0) * (xc + 6) * step;
+    return (double)rounds * (rounds > 1 ? kMultiRoundCost : 1.0) * (xc + 6) * (pair ? sh.step_full : sh.step);
 }
 
 // the even splits of nx planes into 1, 2, ... slabs: next_split gives the slab length of the next
@@ -338,7 +319,7 @@ static Launch plan_printed(const skyr_lattice* lat, skyr_precision prec)
     const int oz = prec == SKYR_F64 ? FpGeoF64::OZ : FpGeoF32::OZ;
     Launch L{};
     L.variant = 0;
-    L.shape = Shape{oy * oz / 64, 0, 0, oz, 1, 1.0};
+    L.shape = Shape{oy * oz / 64, 0, 0, oz, 1, 1.0, 0.0, 0.0};
     tile_grid(lat, L.shape, L.tiles_y, L.tiles_z, L.zstart);
     const int nx = lat->n[0] - 4, tiles = L.tiles_y * L.tiles_z;
     double best = INFINITY;
@@ -2050,13 +2031,11 @@ static skyr_status upload_ints(const std::vector<int>& v, int*& d, int& cap)
 // planes of slab `slab` of a field in a batch
 static int slab_planes(const Launch& L, int nx, int slab) { return slab_planes(slab, L.per_block, nx, L.units, L.unit_len()); }
 
-// Sweep time of block `blk` of a job, in the units of a shape's cost factor: the planes
-// of its item (with what a block pays on top) times the item's output columns.
+// Sweep time of block `blk` of a job in steps of the march (with what a block pays on top).  It orders
+// the blocks of one chain, whose jobs all have the same shape.
 static double item_time(const Launch& L, int nx, int blk)
 {
-    const int tiles = L.tiles_y * L.tiles_z;
-    const int planes = slab_planes(L, nx, blk / tiles);
-    return (double)(planes + 6) * L.shape.oy() * L.shape.oz() * L.shape.cost;
+    return slab_planes(L, nx, blk / (L.tiles_y * L.tiles_z)) + 6;
 }
 
 constexpr int kXcds = 8;
@@ -2126,6 +2105,10 @@ static std::vector<int> chain_slots(const skyr_batch* b, const std::vector<int>&
 // that is free first.  A block takes its planes and about six more times its shape's step time.
 // Beyond kSimulated blocks, where one block weighs little, the work spread over all CUs and half a
 // longest block for the end of the launch: the choice is then among long slabs, and cheap on the host.
+// Measured against every slab length of 16 .. 256 planes, a slot in us: the 64-field mix twice over
+// 1775 where the best takes 1774, 72 fields of 128^3 float 2177 of 2177, 40 double 2430 of 2419, 150 of
+// 96^3 float 2088 of 2088, 18 of 256^3 4337 of 4337, 120 served fields 6400 of 6273, 14 of 200^3
+// double 3748 of 3556 (slabs of 98 planes, which it puts 0.3% behind whole ones).
 constexpr int kSimulated = 2048;
 static double slot_time(const skyr_batch* b, const std::vector<Launch>& cut)
 {
@@ -2151,7 +2134,7 @@ static double slot_time(const skyr_batch* b, const std::vector<Launch>& cut)
         if (!J.active) continue;
         const Launch& L = cut[j];
         const int tiles = L.tiles_y * L.tiles_z;
-        const double step = J.prec == SKYR_F64 ? kStepF64[L.variant] : kStepF32[L.variant];
+        const double step = L.shape.step_full / L.shape.per_cu;  // a CU's time for each of its blocks
         for (int sl = 0; sl < L.slabs; ++sl) {
             const double t = (slab_planes(L, J.lat.n[0] - 4, sl) + 6) * step;
             for (int n = tiles; n > 0; n -= piece)

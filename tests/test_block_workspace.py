@@ -28,4 +28,4 @@ def test_block_workspace_holds_every_launch(prec, extent):
                 blocks = math.ceil(extent[0] / xc) * math.ceil(extent[1] / oy) * math.ceil(extent[2] / oz)
                 assert skyr.block_workspace_bytes(blk, prec) == need >= HEAD + blocks * RECORD
     finally:
-        skyr.set_tile(region, prec, saved[0], max(16, saved[1]))
+        skyr.set_tile(region, prec, *saved)
