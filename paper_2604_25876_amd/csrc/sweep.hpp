@@ -1425,19 +1425,23 @@ __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, S
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tiles = a.tiles_y * a.tiles_z;
     const int x0 = a.olo[0], nx = a.ohi[0] - a.olo[0] + 1;
-    // a block of a batched sweep: its slab, its first unit and how many
+    // a block of a batched sweep: its slab, its first unit and how many, and its first plane and the
+    // one after its last
     const int slab = b / tiles, unit0 = FROM_TABLE ? slab * a.per_block : 0;
     const int own = FROM_TABLE ? min(a.units - unit0, a.per_block) : 0;
-    if constexpr (FROM_TABLE) {  // (read after the march's first barrier)
-        if (tid < own)
-            sm.unit_end[tid] = unit_start(unit0 + tid + 1, nx, a.units, a.unit_len) - unit_start(unit0, nx, a.units, a.unit_len);
+    int first = 0, end = 0;
+    if constexpr (FROM_TABLE) {
+        first = __builtin_amdgcn_readfirstlane(unit_start(unit0, nx, a.units, a.unit_len));
+        end = __builtin_amdgcn_readfirstlane(unit_start(unit0 + own, nx, a.units, a.unit_len));
+        // (read after the march's first barrier)
+        if (tid < own) sm.unit_end[tid] = unit_start(unit0 + tid + 1, nx, a.units, a.unit_len) - first;
         if (tid < G::NWI) sm.units_ended[tid] = 0;
     }
     const auto segment = [&](int item) {
         Segment s = item_segment(item, tiles, a.tiles_z, x0, nx, a.xchunk);
         if constexpr (FROM_TABLE) {
-            s.xa = x0 + unit_start(unit0, nx, a.units, a.unit_len);
-            s.xe = x0 + unit_start(unit0 + own, nx, a.units, a.unit_len);
+            s.xa = x0 + first;
+            s.xe = x0 + end;
         }
         return s;
     };

@@ -34,7 +34,7 @@ def cut(tmp_path_factory):
 
 # the smallest; around the units' lengths; below and above 185,352 planes, from where the last unit's
 # number times the planes passes 2^31; the longest lattice of 5 x 5 rows that is accepted
-@pytest.mark.parametrize("nx", list(range(1, 70)) + [124, 127, 252, 256, 257, 1000, 65535, 185351, 185352, 185400,
+@pytest.mark.parametrize("nx", list(range(1, 70)) + [124, 127, 252, 256, 257, 1000, 65535, 65536, 185351, 185352, 185400,
                                                      200000, 1342173, 2 ** 29 // 25 - 4])
 def test_units_and_slabs(cut, nx):
     units = cut.u_default(nx)
