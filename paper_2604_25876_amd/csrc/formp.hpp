@@ -525,7 +525,7 @@ void formp_kernel(SweepArgs a)
         __syncthreads();  // the next item's first planes reuse the buffers
     }
 
-    block_sums<G::NW, MODE == MODE_STEP>(fp.pe2, (double)fp.pf2 * k.dinvK2, fp.pp * k.dinvK, fp.pe4, fp.pe0,
+    block_sums<G::NW, MODE == MODE_STEP>(fp.pe2, (double)fp.pf2, fp.pp, k.dinvK2, k.dinvK, fp.pe4, fp.pe0,
                                          fp.pb_sum * k.dinv12h3, 0.0, a.partials + (size_t)b * NPART, sm);
     if constexpr (MODE == MODE_STEP)
         finish_step<G::THREADS, G::NW, NPART, P_E2, P_F2, P_POW>(a.partials, nb, nb, a.ctl, cm.restore != RESTORE_NONE, sm);

@@ -391,46 +391,46 @@ template <int CTRL> __device__ __forceinline__ double dpp_f64(double v)
     const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
-// The stages of a wave's sums below: lanes 32 and 16 away (a swap of two copies' halves, or of their
-// rows, leaves one's in one copy and the other's in the other), then 8, 4, 2 and 1 away within a row
-// of 16: the order of a butterfly, the same in wave_total and wave_totals, so that a sum does not
-// depend on which of them formed it.
-template <bool MAX, class Swap> __device__ __forceinline__ double wave_halves(double a, double b, Swap swap)
-{
-    const unsigned long long ua = __builtin_bit_cast(unsigned long long, a), ub = __builtin_bit_cast(unsigned long long, b);
-    const auto lo = swap((unsigned)ua, (unsigned)ub), hi = swap((unsigned)(ua >> 32), (unsigned)(ub >> 32));
-    const double x = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
-    const double y = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
-    return MAX ? fmax(x, y) : x + y;
-}
-// the stages below 32 lanes
-template <bool MAX> __device__ __forceinline__ double wave_rows(double v)
+// The stages of a wave's sums after the first: lanes 2 away, 8 and 4 away within a row of 16 (turns of
+// the row: lanes 8 apart being equal after the first turn, 4 below is 4 above), then rows and halves
+// (a swap of two copies' rows leaves one's in one copy and the other's in the other).  The order is
+// that of wave_total and wave_totals alike: a sum does not depend on which of them formed it.  (With
+// the swaps first the block ends took longer: 40^3 double 5800 us for 300 steps against 5760.)
+template <bool MAX> __device__ __forceinline__ double wave_stages(double v)
 {
     const auto add = [](double a, double b) { return MAX ? fmax(a, b) : a + b; };
-    v = wave_halves<MAX>(v, v, [](unsigned x, unsigned y) { return __builtin_amdgcn_permlane16_swap(x, y, false, false); });
-    v = add(v, dpp_f64<0x128>(v));  // turned by 8 lanes of 16
-    v = add(v, dpp_f64<0x124>(v));  // by 4 (lanes 8 apart being equal, 4 away)
     v = add(v, dpp_f64<0x4e>(v));   // quad lanes 2, 3, 0, 1
-    v = add(v, dpp_f64<0xb1>(v));   // quad lanes 1, 0, 3, 2
+    v = add(v, dpp_f64<0x128>(v));  // turned by 8 lanes of 16
+    v = add(v, dpp_f64<0x124>(v));  // by 4
+    const auto halves = [&](auto swap) {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        const auto lo = swap((unsigned)u), hi = swap((unsigned)(u >> 32));
+        const double x = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
+        const double y = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+        return add(x, y);
+    };
+    v = halves([](unsigned u) { return __builtin_amdgcn_permlane16_swap(u, u, false, false); });
+    v = halves([](unsigned u) { return __builtin_amdgcn_permlane32_swap(u, u, false, false); });
     return v;
 }
 // the sum (maximum) of v over the wave, in every lane
 template <bool MAX> __device__ __forceinline__ double wave_total(double v)
 {
-    return wave_rows<MAX>(
-        wave_halves<MAX>(v, v, [](unsigned x, unsigned y) { return __builtin_amdgcn_permlane32_swap(x, y, false, false); }));
+    const double w = dpp_f64<0xb1>(v);  // quad lanes 1, 0, 3, 2
+    return wave_stages<MAX>(MAX ? fmax(v, w) : v + w);
 }
 
-// a and b summed over the wave: a in lanes 0 .. 31, b in lanes 32 .. 63 from the first stage on
-// (two sums for little more than one); every lane of the lower half ends with a's, all with b's total
+// a and b summed over the wave: a in the even lanes, b in the odd ones from the first stage on (two
+// sums for little more than one; every later stage goes an even number of lanes); the even lanes end
+// with a's, all with b's total
 __device__ __forceinline__ void wave_totals(double& a, double& b)
 {
-    const double v = wave_rows<false>(
-        wave_halves<false>(a, b, [](unsigned x, unsigned y) { return __builtin_amdgcn_permlane32_swap(x, y, false, false); }));
+    const bool odd = threadIdx.x & 1;
+    const double v = wave_stages<false>((odd ? b : a) + dpp_f64<0xb1>(odd ? a : b));
     const unsigned long long w = __builtin_bit_cast(unsigned long long, v);
     a = v;
-    b = __builtin_bit_cast(double, ((unsigned long long)__builtin_amdgcn_readlane((unsigned)(w >> 32), 32) << 32) |
-                                       (unsigned)__builtin_amdgcn_readlane((unsigned)w, 32));
+    b = __builtin_bit_cast(double, ((unsigned long long)__builtin_amdgcn_readlane((unsigned)(w >> 32), 1) << 32) |
+                                       (unsigned)__builtin_amdgcn_readlane((unsigned)w, 1));
 }
 // the largest of the non-negative v over the wave, in every lane
 __device__ __forceinline__ double wave_most(double v) { return wave_total<true>(v); }
@@ -876,12 +876,12 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT, int STREAM> s
             if (st >= last - xa + 4) return true;
             const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
             const int u = __builtin_amdgcn_readfirstlane(sm.units_ended[wave]);
-            double e = pe2, p = pp * k.dinvK;
+            double e = pe2, p = pp;
             wave_totals(e, p);
             const T f = wave_most(pf2);
             if ((threadIdx.x & 63) == 0) {
                 sm.unit[u][wave][U_E] = e;
-                sm.unit[u][wave][U_F2] = (double)f * k.dinvK2;
+                sm.unit[u][wave][U_F2] = (double)f;
                 sm.unit[u][wave][U_POW] = p;
                 sm.units_ended[wave] = u + 1;
             }
@@ -1281,10 +1281,11 @@ __device__ __forceinline__ void finish_step(const double* part, int nb, int reco
 
 // A block's sums over its threads, in a fixed order (a butterfly per wave, then waves 0 .. NWS-1),
 // published as the block's record.  e2: in a step sweep the whole energy density (the parts and the
-// charge are then not summed).  Lane i of wave 0 publishes slot i.
+// charge are then not summed).  Lane i of wave 0 publishes slot i.  f2 and pw come unscaled and are
+// scaled in the record, as those of a batched sweep.
 template <int NWS, bool STEP, class Smem>
-__device__ __forceinline__ void block_sums(double e2, double f2, double pw, double e4, double e0, double b, double e6,
-                                           double* record, Smem& sm)
+__device__ __forceinline__ void block_sums(double e2, double f2, double pw, double f2_scale, double pw_scale, double e4,
+                                           double e0, double b, double e6, double* record, Smem& sm)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (wave < NWS) {
@@ -1319,7 +1320,8 @@ __device__ __forceinline__ void block_sums(double e2, double f2, double pw, doub
             sum += v;
             most = fmax(most, v);
         }
-        __hip_atomic_store(record + i, i == P_F2 ? most : sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(record + i, i == P_F2 ? most * f2_scale : i == P_POW ? sum * pw_scale : sum, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -1327,8 +1329,8 @@ __device__ __forceinline__ void block_sums(double e2, double f2, double pw, doub
 // the waves' sums over the `before` units before the last and the threads' over the last.  Lane
 // 3 u + q of wave 0 publishes sum q of unit u.
 template <int NWS, class Smem>
-__device__ __forceinline__ void unit_sums(double e, double f2, double pw, int before, double* record, int stride,
-                                          Smem& sm)
+__device__ __forceinline__ void unit_sums(double e, double f2, double pw, double f2_scale, double pw_scale, int before,
+                                          double* record, int stride, Smem& sm)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (wave < NWS) {
@@ -1351,7 +1353,8 @@ __device__ __forceinline__ void unit_sums(double e, double f2, double pw, int be
             sum += v;
             most = fmax(most, v);
         }
-        __hip_atomic_store(record + (size_t)u * stride + q, q == U_F2 ? most : sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(record + (size_t)u * stride + q, q == U_E ? sum : q == U_F2 ? most * f2_scale : sum * pw_scale, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -1470,12 +1473,12 @@ __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, S
     }
     if constexpr (FROM_TABLE) {
         // the records of the block's units, in the order of the units and tiles of the field
-        unit_sums<G::NWI>(e2, f2 * k.dinvK2, pw * k.dinvK, own - 1,
+        unit_sums<G::NWI>(e2, f2, pw, k.dinvK2, k.dinvK, own - 1,
                           a.partials + (size_t)(unit0 * tiles + b - slab * tiles) * UNIT_REC, tiles * UNIT_REC, sm);
         finish_step<G::THREADS, G::NW, UNIT_REC, U_E, U_F2, U_POW>(a.partials, nb, tiles * a.units, a.ctl,
                                                                    cm.restore != RESTORE_NONE, sm);
     } else {
-        block_sums<G::NWI, MODE == MODE_STEP>(e2, f2 * k.dinvK2, pw * k.dinvK, e4, e0, bsum, e6, a.partials + (size_t)b * NPART, sm);
+        block_sums<G::NWI, MODE == MODE_STEP>(e2, f2, pw, k.dinvK2, k.dinvK, e4, e0, bsum, e6, a.partials + (size_t)b * NPART, sm);
         if constexpr (MODE == MODE_STEP)
             finish_step<G::THREADS, G::NW, NPART, P_E2, P_F2, P_POW>(a.partials, nb, nb, a.ctl,
                                                                      cm.restore != RESTORE_NONE, sm);
