@@ -14,8 +14,9 @@ const void* step_kernel(skyr_precision prec, int variant, int ext, int stream, i
 const void* grad_kernel(skyr_precision prec, int variant, int ext, int& threads);
 // step sweep of a batch's fields (cache policy STREAM_NONE or STREAM_STORES)
 const void* batch_kernel(skyr_precision prec, int variant, int ext, int stream, int& threads);
-// printed-form sweep of one field (ext: the extra potentials or the gradient flow)
-const void* printed_kernel(skyr_precision prec, int mode, bool ext, int stream, int& threads);
+// printed-form sweep of one field (ext: the extra potentials or the gradient flow; groups: the steps of
+// every slab's march are whole groups of five)
+const void* printed_kernel(skyr_precision prec, int mode, bool ext, int stream, bool groups, int& threads);
 
 // per precision, in files of their own
 template <typename T> const void* step_kernel_of(int variant, int ext, int stream, int& threads);

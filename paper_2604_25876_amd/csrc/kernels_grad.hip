@@ -47,24 +47,27 @@ const void* batch_kernel(skyr_precision prec, int variant, int ext, int stream, 
                             : batch_kernel_of<float>(variant, ext, stream, threads);
 }
 
-template <typename T, int MODE, bool EXT> static const void* printed_of(int stream)
+template <typename T, int MODE, bool EXT, bool GROUPS> static const void* printed_of(int stream)
 {
     if constexpr (MODE == MODE_STEP) {
-        if (stream == STREAM_NONE) return (const void*)formp_kernel<T, MODE, EXT, STREAM_NONE>;
-        if (stream == STREAM_STORES) return (const void*)formp_kernel<T, MODE, EXT, STREAM_STORES>;
+        if (stream == STREAM_NONE) return (const void*)formp_kernel<T, MODE, EXT, STREAM_NONE, GROUPS>;
+        if (stream == STREAM_STORES) return (const void*)formp_kernel<T, MODE, EXT, STREAM_STORES, GROUPS>;
     }
-    return (const void*)formp_kernel<T, MODE, EXT, STREAM_ALL>;
+    return (const void*)formp_kernel<T, MODE, EXT, STREAM_ALL, GROUPS>;
 }
-template <typename T> static const void* printed_of(int mode, bool ext, int stream)
+template <typename T> static const void* printed_of(int mode, bool ext, int stream, bool groups)
 {
-    if (mode == MODE_STEP) return ext ? printed_of<T, MODE_STEP, true>(stream) : printed_of<T, MODE_STEP, false>(stream);
-    return ext ? printed_of<T, MODE_GRAD, true>(stream) : printed_of<T, MODE_GRAD, false>(stream);
+    if (mode != MODE_STEP)
+        return ext ? printed_of<T, MODE_GRAD, true, false>(stream) : printed_of<T, MODE_GRAD, false, false>(stream);
+    if constexpr (sizeof(T) == 4)
+        if (groups) return ext ? printed_of<T, MODE_STEP, true, true>(stream) : printed_of<T, MODE_STEP, false, true>(stream);
+    return ext ? printed_of<T, MODE_STEP, true, false>(stream) : printed_of<T, MODE_STEP, false, false>(stream);
 }
 
-const void* printed_kernel(skyr_precision prec, int mode, bool ext, int stream, int& threads)
+const void* printed_kernel(skyr_precision prec, int mode, bool ext, int stream, bool groups, int& threads)
 {
     threads = prec == SKYR_F64 ? FpGeoF64::THREADS : FpGeoF32::THREADS;
-    return prec == SKYR_F64 ? printed_of<double>(mode, ext, stream) : printed_of<float>(mode, ext, stream);
+    return prec == SKYR_F64 ? printed_of<double>(mode, ext, stream, groups) : printed_of<float>(mode, ext, stream, groups);
 }
 
 }  // namespace skyr

@@ -610,11 +610,18 @@ static hipError_t sweep(skyr_precision prec, int mode, const Launch& L, const Sw
     return hipLaunchKernel(fn, dim3(L.blocks()), dim3(threads), argv, 0, s);
 }
 
+// whether the steps of every slab's march, four more than its planes, are whole groups of five
+static bool whole_groups(const SweepArgs& a)
+{
+    const int nx = a.ohi[0] - a.olo[0] + 1, last = nx - (nx - 1) / a.xchunk * a.xchunk;
+    return (last + 4) % 5 == 0 && (nx == last || (a.xchunk + 4) % 5 == 0);
+}
+
 // The printed-form sweep: one launch, arguments made by make_args with plan_printed's launch.
 static hipError_t sweep_printed(skyr_precision prec, int mode, const Launch& L, const SweepArgs& args, hipStream_t s)
 {
     int threads = 0;
-    const void* fn = printed_kernel(prec, mode, ext_level(args) != EXT_NONE, args.stream, threads);
+    const void* fn = printed_kernel(prec, mode, ext_level(args) != EXT_NONE, args.stream, whole_groups(args), threads);
     void* argv[1] = {const_cast<SweepArgs*>(&args)};
     return hipLaunchKernel(fn, dim3(L.blocks()), dim3(threads), argv, 0, s);
 }
@@ -1251,7 +1258,7 @@ static skyr_status anf_run(const skyr_lattice* lat, skyr_precision prec, const s
         if (graphs && group >= kFlowGraphSweeps) {
             const int reps = (int)(group / kFlowGraphSweeps);
             int threads = 0;
-            const void* fn = printed ? printed_kernel(prec, MODE_STEP, ext_level(a) != EXT_NONE, a.stream, threads)
+            const void* fn = printed ? printed_kernel(prec, MODE_STEP, ext_level(a) != EXT_NONE, a.stream, whole_groups(a), threads)
                                      : step_kernel(prec, L.variant, ext_level(a), a.stream, threads);
             const skyr_status rc = flow_graph_launch(fn, L.blocks(), threads, a, reps, s);
             if (rc != SKYR_OK) return rc;
