@@ -8,7 +8,8 @@ import pytest
 
 from paper_2604_25876_amd import skyr
 
-SHAPES = [(5, 5, 5), (9, 40, 40), (19, 30, 30), (20, 30, 30), (21, 18, 70)]
+# (lattices that no other test sets a tile of)
+SHAPES = [(5, 7, 6), (9, 41, 40), (19, 30, 31), (20, 30, 31), (21, 18, 71)]
 
 
 @pytest.mark.parametrize("prec", [skyr.F64, skyr.F32_BULK])
@@ -30,11 +31,11 @@ def test_default_tile_can_be_set_again(prec, n):
 
 
 def test_saved_choice_of_a_small_lattice(tmp_path, monkeypatch):
-    lat = skyr.Lattice((ctypes.c_int32 * 3)(9, 40, 40), 0, 0.2)
+    lat = skyr.Lattice((ctypes.c_int32 * 3)(9, 42, 40), 0, 0.2)
     v, xc = skyr.get_tile(lat, skyr.F64)
     assert xc < 16
     path = tmp_path / "tune.json"
-    path.write_text(json.dumps({"9x40x40:f64": {"variant": v, "xchunk": xc, "us": 20.0}}))
+    path.write_text(json.dumps({"9x42x40:f64": {"variant": v, "xchunk": xc, "us": 20.0}}))
     monkeypatch.setenv("SKYR_TUNE_CACHE", str(path))
     got = skyr.autotune_cached(lat, skyr.F64, skyr.Model(1.0), skyr.Flow(0.01, 0.0, 1, 0, 0), None, None, None, None)
     assert got == (v, xc, 20.0)
