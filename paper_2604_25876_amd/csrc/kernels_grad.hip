@@ -5,7 +5,8 @@
 
 namespace skyr {
 
-template <typename T, class G> static const void* grad_of(int ext, int, int& threads)
+// Their one output is written once and read by no sweep after them: streamed whatever its size.
+template <typename T, class G> static const void* grad_of(int ext, int& threads)
 {
     threads = G::THREADS;
     if (ext == EXT_SEXTIC) return (const void*)sweep_kernel<T, G, MODE_GRAD, EXT_SEXTIC, STREAM_ALL>;
@@ -15,18 +16,17 @@ template <typename T, class G> static const void* grad_of(int ext, int, int& thr
 
 const void* grad_kernel(skyr_precision prec, int variant, int ext, int& threads)
 {
-    const int stream = STREAM_ALL;
     if (prec == SKYR_F64) {
         int v = 0;
 #define SKYR_CASE(a, b, c, d, ...) \
-    if (variant == v) return grad_of<double, Geo<a, b, c, d>>(ext, stream, threads); \
+    if (variant == v) return grad_of<double, Geo<a, b, c, d>>(ext, threads); \
     ++v;
         SKYR_SHAPES_F64(SKYR_CASE)
 #undef SKYR_CASE
     } else {
         int v = 0;
 #define SKYR_CASE(a, b, c, d, ...) \
-    if (variant == v) return grad_of<float, Geo<a, b, c, d>>(ext, stream, threads); \
+    if (variant == v) return grad_of<float, Geo<a, b, c, d>>(ext, threads); \
     ++v;
         SKYR_SHAPES_F32(SKYR_CASE)
 #undef SKYR_CASE

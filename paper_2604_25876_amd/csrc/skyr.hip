@@ -339,7 +339,7 @@ static Launch plan_printed(const skyr_lattice* lat, skyr_precision prec)
 }
 
 constexpr size_t CTL_BYTES = 256;
-// observables (8 doubles), then the moments' centre (4 doubles at +64) and result (at +128)
+// observables (8 doubles), then the moments' centre (5 doubles at +64) and result (at +128)
 constexpr size_t OBS_BYTES = 512;
 constexpr size_t MOM_CENTRE_OFFSET = 64;
 constexpr size_t MOM_OUT_OFFSET = 128;

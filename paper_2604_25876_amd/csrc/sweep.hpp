@@ -477,7 +477,7 @@ template <typename T, bool FROM_TABLE> struct SweepCommon {
     gptr<T> pout[4];
     gptr<T> vel[4];
     gptr<T> gout[4];
-    long long cs;        // bytes from one component to the next
+    long long cs;        // bytes from one component to the next (set and read by the printed form alone)
     int n0, n1, n2;
     int zlo, zhi;        // the columns of a row a load may touch
     int ilo[3], ihi[3];  // I in array coordinates
@@ -1416,7 +1416,6 @@ __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, S
             cm.vel[A] = (gptr<T>)(pvel ? pvel + A * N3 : nullptr);
             cm.gout[A] = (gptr<T>)(pgrad ? pgrad + A * N3 : nullptr);
         }
-        cm.cs = N3 * (long long)sizeof(T);
     }
     cm.has_grad = a.grad != nullptr;
     cm.projected = a.projected != 0;
