@@ -111,10 +111,10 @@ static Launch plan_with(const skyr_lattice* lat, skyr_precision prec, int varian
     Launch L{};
     L.variant = variant;
     L.shape = shape_of(prec, variant);
-    L.xchunk = xchunk;
     tile_grid(lat, L.shape, L.tiles_y, L.tiles_z, L.zstart);
     const int nx = lat->n[0] - 4;
-    L.slabs = (nx + xchunk - 1) / xchunk;
+    L.xchunk = std::min(xchunk, nx);  // (any length may be set: a longer slab is the whole of x)
+    L.slabs = (nx + L.xchunk - 1) / L.xchunk;
     L.units = L.slabs;
     L.per_block = 1;
     return L;
