@@ -170,8 +170,8 @@ static void default_tile(const skyr_lattice* lat, skyr_precision prec, int& v_ou
 // times the time of a step of its shape, 15% more when r > 1.  With the shapes' step times this picks
 // within 1.2% of the fastest of all (shape, slab length) pairs, measured on cubes of 40 .. 256
 // sites in both precisions: one round with as many slabs as it holds, where the lattice is small
-// enough.  40^3: 2-plane slabs, 108-162 blocks, 19-21 us a sweep against 42-43.5 with the default
-// tile's 18 blocks; 96^3: 31 / 39 us (float / double) against 44 / 47; 128^3 float 41 against 44;
+// enough.  40^3: 2-plane slabs, 108-162 blocks, 17.5 us a sweep (19-21 when the pairs were measured,
+// before the ends of blocks got shorter) against 42-43.5 with the default tile's 18 blocks; 96^3: 31 / 39 us (float / double) against 44 / 47; 128^3 float 41 against 44;
 // 256^3 double on 8 x 32 tiles 451 against 478.
 // no launch has more blocks than every workspace (and the fixed scratch) has records for
 constexpr int kMaxBlocks = 4084;
@@ -495,8 +495,8 @@ template <typename T> __global__ void fill_kernel(T* __restrict__ p, long long n
 // The frozen layers (everything outside the interior) of dst: those of src, or zero where src is
 // null.  Only frozen sites are visited: the whole rows beside x and y faces, element by element, then
 // the four end columns of every other row.  (Testing every site of the lattice, with its divisions,
-// took 52 us on 256^3; zeroing a whole gradient before its sweep wrote 110 MB on 151^3 double.)
-// A gradient call on 151^3 double 148 -> 136 us; a flow call on 256^3 starts 50 us sooner.
+// took 45 us on 256^3 float and 56 double against 33 and 35 now, 14 on 151^3 against 6 and 9; zeroing a
+// whole gradient before its sweep wrote 110 MB on 151^3 double: a call there 148 -> 136 us.)
 template <typename T>
 __global__ void frozen_kernel(const T* __restrict__ src, T* __restrict__ dst, int n0, int n1, int n2)
 {
