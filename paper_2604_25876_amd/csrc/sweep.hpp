@@ -42,6 +42,7 @@
 
 #include "../../include/skyr.h"
 #include "cut.hpp"
+#include "shapes.hpp"
 
 #include <type_traits>
 
@@ -337,6 +338,25 @@ template <typename T, class G> struct SweepSmem {
 // potentials (m_y, m_z, m_w) and the gradient flow; 2 also the sextic term.  The levels
 // are separate kernels so that each carries only the registers it needs.
 enum : int { EXT_NONE = 0, EXT_POT = 1, EXT_SEXTIC = 2 };
+
+// Waves per SIMD that a kernel leaves registers for: those of the blocks its shape has on a CU
+// (shapes.hpp).  At 131 registers, three more than that allows, the second float shape had one block
+// on a CU instead of two: 40 x 5 x 20000 sites 156 us a sweep against 120, 300 x 12 x 1500 97 against 80.
+// The sextic kernels need more and have one block a CU in every shape.
+template <typename T, class G, int EXT> constexpr int waves_per_simd()
+{
+    int blocks = 1;
+    const auto look = [&](const Shape& s) {
+        if (s.nwi == G::NWI && s.nwh == G::NWH && s.hpt == G::HPT && s.cols == G::OZ) blocks = s.per_cu;
+    };
+    if (EXT != EXT_SEXTIC) {
+        if (sizeof(T) == 8)
+            for (const Shape& s : kShapesF64) look(s);
+        else
+            for (const Shape& s : kShapesF32) look(s);
+    }
+    return blocks * G::NW / 4;
+}
 
 // Per-launch constants.  With a^ = 12 h a (the scaled first difference), G^ = (12 h)^2 G,
 // Q^ = (12 h)^3 Q and L^ = 12 h^2 Lap, the scaled gradient g^ = K g, K = (12 h)^4, is
@@ -876,12 +896,12 @@ template <typename T, class G, int MODE, bool FROM_TABLE, int EXT, int STREAM> s
             if (st >= last - xa + 4) return true;
             const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
             const int u = __builtin_amdgcn_readfirstlane(sm.units_ended[wave]);
-            double e = pe2, p = pp;
+            double e = pe2, p = pp * k.dinvK;
             wave_totals(e, p);
             const T f = wave_most(pf2);
             if ((threadIdx.x & 63) == 0) {
                 sm.unit[u][wave][U_E] = e;
-                sm.unit[u][wave][U_F2] = (double)f;
+                sm.unit[u][wave][U_F2] = (double)f * k.dinvK2;
                 sm.unit[u][wave][U_POW] = p;
                 sm.units_ended[wave] = u + 1;
             }
@@ -1281,8 +1301,8 @@ __device__ __forceinline__ void finish_step(const double* part, int nb, int reco
 
 // A block's sums over its threads, in a fixed order (a butterfly per wave, then waves 0 .. NWS-1),
 // published as the block's record.  e2: in a step sweep the whole energy density (the parts and the
-// charge are then not summed).  Lane i of wave 0 publishes slot i.  f2 and pw come unscaled and are
-// scaled in the record, as those of a batched sweep.
+// charge are then not summed).  Lane i of wave 0 publishes slot i, f2 and pw with the
+// factors given.
 template <int NWS, bool STEP, class Smem>
 __device__ __forceinline__ void block_sums(double e2, double f2, double pw, double f2_scale, double pw_scale, double e4,
                                            double e0, double b, double e6, double* record, Smem& sm)
@@ -1329,8 +1349,8 @@ __device__ __forceinline__ void block_sums(double e2, double f2, double pw, doub
 // the waves' sums over the `before` units before the last and the threads' over the last.  Lane
 // 3 u + q of wave 0 publishes sum q of unit u.
 template <int NWS, class Smem>
-__device__ __forceinline__ void unit_sums(double e, double f2, double pw, double f2_scale, double pw_scale, int before,
-                                          double* record, int stride, Smem& sm)
+__device__ __forceinline__ void unit_sums(double e, double f2, double pw, int before, double* record, int stride,
+                                          Smem& sm)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (wave < NWS) {
@@ -1353,8 +1373,7 @@ __device__ __forceinline__ void unit_sums(double e, double f2, double pw, double
             sum += v;
             most = fmax(most, v);
         }
-        __hip_atomic_store(record + (size_t)u * stride + q, q == U_E ? sum : q == U_F2 ? most * f2_scale : sum * pw_scale, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(record + (size_t)u * stride + q, q == U_F2 ? most : sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -1449,7 +1468,7 @@ __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, S
     };
     const int items = FROM_TABLE ? nb : tiles * ((nx + a.xchunk - 1) / a.xchunk);
 
-    double e2 = 0.0, e4 = 0.0, e0 = 0.0, e6 = 0.0, bsum = 0.0, f2 = 0.0, pw = 0.0;  // f2, pw: scaled
+    double e2 = 0.0, e4 = 0.0, e0 = 0.0, e6 = 0.0, bsum = 0.0, f2 = 0.0, pw = 0.0;
     if (wave < G::NWI) {
         Interior<T, G, MODE, FROM_TABLE, EXT, STREAM> it(sm, k, cm, tid);
         for (int item = b; item < items; item += nb) {
@@ -1460,8 +1479,8 @@ __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, S
         e4 = it.pe4;
         e0 = it.pe0;
         bsum = it.pb_sum * k.dinv12h3;
-        f2 = (double)it.pf2;
-        pw = it.pp;
+        f2 = (double)it.pf2 * k.dinvK2;  // (scaled here: after the roles meet it cost four registers)
+        pw = it.pp * k.dinvK;
         e6 = it.pe6;
     } else {
         Halo<T, G, FROM_TABLE, EXT> hl(sm, k, cm, tid - G::NWI * 64);
@@ -1472,12 +1491,12 @@ __device__ __forceinline__ void sweep_block(const SweepArgs& a, int b, int nb, S
     }
     if constexpr (FROM_TABLE) {
         // the records of the block's units, in the order of the units and tiles of the field
-        unit_sums<G::NWI>(e2, f2, pw, k.dinvK2, k.dinvK, own - 1,
+        unit_sums<G::NWI>(e2, f2, pw, own - 1,
                           a.partials + (size_t)(unit0 * tiles + b - slab * tiles) * UNIT_REC, tiles * UNIT_REC, sm);
         finish_step<G::THREADS, G::NW, UNIT_REC, U_E, U_F2, U_POW>(a.partials, nb, tiles * a.units, a.ctl,
                                                                    cm.restore != RESTORE_NONE, sm);
     } else {
-        block_sums<G::NWI, MODE == MODE_STEP>(e2, f2, pw, k.dinvK2, k.dinvK, e4, e0, bsum, e6, a.partials + (size_t)b * NPART, sm);
+        block_sums<G::NWI, MODE == MODE_STEP>(e2, f2, pw, 1.0, 1.0, e4, e0, bsum, e6, a.partials + (size_t)b * NPART, sm);
         if constexpr (MODE == MODE_STEP)
             finish_step<G::THREADS, G::NW, NPART, P_E2, P_F2, P_POW>(a.partials, nb, nb, a.ctl,
                                                                      cm.restore != RESTORE_NONE, sm);
@@ -1495,7 +1514,7 @@ __device__ __forceinline__ int xcd_logical_block(int i, int n)
 }
 
 template <typename T, class G, int MODE, int EXT, int STREAM>
-__global__ __launch_bounds__(G::THREADS) void sweep_kernel(SweepArgs a)
+__global__ __launch_bounds__(G::THREADS, (waves_per_simd<T, G, EXT>())) void sweep_kernel(SweepArgs a)
 {
     __shared__ SweepSmem<T, G> smem;
     const int nb = gridDim.x;
@@ -1508,9 +1527,8 @@ __global__ __launch_bounds__(G::THREADS) void sweep_kernel(SweepArgs a)
 // p mod 8); a field's sums are taken per unit of planes, in the order of the units and tiles, and do not
 // depend on how many units its blocks march through.
 template <typename T, class G, int EXT, int STREAM>
-__global__ __launch_bounds__(G::THREADS) void batch_sweep_kernel(const SweepArgs* __restrict__ jobs,
-                                                                 const int2* __restrict__ slot,
-                                                                 const int* __restrict__ blocks_of_job)
+__global__ __launch_bounds__(G::THREADS, (waves_per_simd<T, G, EXT>())) void batch_sweep_kernel(
+    const SweepArgs* __restrict__ jobs, const int2* __restrict__ slot, const int* __restrict__ blocks_of_job)
 {
     __shared__ SweepSmem<T, G> smem;
     const int2 e = slot[blockIdx.x];
