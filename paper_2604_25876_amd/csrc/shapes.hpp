@@ -6,17 +6,21 @@
 //   COST       the relative time of one output site and plane in a full round of the chip, measured
 //              at 256^3, by which the default tile is chosen (the one that is reported and that saved
 //              settings name: a rule that stays as it is);
-//   STEP       microseconds of one step of the march with one block on a CU,
-//   STEP_FULL  and with PER_CU blocks on each, by which launches are chosen: those of a lattice on its
-//              default tile and the slabs of batches.
-// COST prices the 16 x 16 and the 8 x 32 double tile alike, STEP the second 5% lower: it was measured
-// on the sweep as it is, over lattices of 40 .. 256 sites.  A build may define its own lists (one
-// shape per precision for a quick build, say) before this header.
+//   STEP       microseconds of one step of the march in a launch of one round of one block a CU,
+//   STEP_FULL  and in one that fills the chip further (PER_CU blocks on a CU; several rounds, for which
+//              a factor comes on top), by which launches are chosen: those of a lattice on its default
+//              tile and the slabs of batches.
+// COST prices the 16 x 16 and the 8 x 32 double tile alike; STEP was measured on the sweep as it is, over
+// cubes of 40 .. 256 sites.  The double STEP_FULLs are fitted to the times of all shapes and up to twelve
+// slab lengths on 90 lattices of 1 .. 16 million sites and checked on 130 others: the choice is 0.6% off the
+// fastest in the mean, 6% at worst; with STEP in their place it was 1.7% and 21% (5 x 2000 x 300 sites, 8 x 32 tiles
+// taken at 146 us where 12 x 32 take 121).  The same fit gained nothing for float.  A build may define
+// its own lists (one shape per precision for a quick build, say) before this header.
 #pragma once
 
 #ifndef SKYR_SHAPES_F64
 #define SKYR_SHAPES_F64(X) \
-    X(4, 4, 1, 16, 1, 1.0, 1.6, 1.6) X(4, 4, 1, 32, 1, 1.02, 1.52, 1.52) X(6, 2, 2, 32, 1, 0.95, 2.2, 2.2)
+    X(4, 4, 1, 16, 1, 1.0, 1.6, 1.65) X(4, 4, 1, 32, 1, 1.02, 1.51, 1.45) X(6, 2, 2, 32, 1, 0.95, 2.17, 1.95)
 #endif
 #ifndef SKYR_SHAPES_F32
 #define SKYR_SHAPES_F32(X) \

@@ -169,7 +169,7 @@ static void default_tile(const skyr_lattice* lat, skyr_precision prec, int& v_ou
 // about two more (its first loads, its sums); a launch of r rounds of the chip takes r (xc + 6)
 // times the time of a step of its shape, 15% more when r > 1.  With the shapes' step times this picks
 // within 1.2% of the fastest of all (shape, slab length) pairs, measured on cubes of 40 .. 256
-// sites in both precisions: one round with as many slabs as it holds, where the lattice is small
+// sites in both precisions (lattices of other proportions: shapes.hpp): one round with as many slabs as it holds, where the lattice is small
 // enough.  40^3: 2-plane slabs, 108-162 blocks, 17.5 us a sweep (19-21 when the pairs were measured,
 // before the ends of blocks got shorter) against 42-43.5 with the default tile's 18 blocks; 96^3: 31 / 39 us (float / double) against 44 / 47; 128^3 float 41 against 44;
 // 256^3 double on 8 x 32 tiles 451 against 478.
@@ -182,7 +182,7 @@ static double launch_cost(skyr_precision prec, int v, int xc, long long blocks)
     const bool pair = sh.per_cu > 1 && blocks > kCUs;
     const long long per_round = (long long)kCUs * (pair ? sh.per_cu : 1);
     const long long rounds = (blocks + per_round - 1) / per_round;
-    return (double)rounds * (rounds > 1 ? kMultiRoundCost : 1.0) * (xc + 6) * (pair ? sh.step_full : sh.step);
+    return (double)rounds * (rounds > 1 ? kMultiRoundCost : 1.0) * (xc + 6) * (pair || rounds > 1 ? sh.step_full : sh.step);
 }
 
 // the even splits of nx planes into 1, 2, ... slabs: next_split gives the slab length of the next
@@ -2141,7 +2141,8 @@ static double slot_time(const skyr_batch* b, const std::vector<Launch>& cut)
         if (!J.active) continue;
         const Launch& L = cut[j];
         const int tiles = L.tiles_y * L.tiles_z;
-        const double step = L.shape.step_full / L.shape.per_cu;  // a CU's time for each of its blocks
+        // a CU's time for each of its blocks
+        const double step = L.shape.per_cu > 1 ? L.shape.step_full / L.shape.per_cu : L.shape.step;
         for (int sl = 0; sl < L.slabs; ++sl) {
             const double t = (slab_planes(L, J.lat.n[0] - 4, sl) + 6) * step;
             for (int n = tiles; n > 0; n -= piece)
