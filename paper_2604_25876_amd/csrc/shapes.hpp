@@ -11,20 +11,22 @@
 //              a factor comes on top), by which launches are chosen: those of a lattice on its default
 //              tile and the slabs of batches.
 // COST prices the 16 x 16 and the 8 x 32 double tile alike; STEP was measured on the sweep as it is, over
-// cubes of 40 .. 256 sites.  The double STEP_FULLs are fitted to the times of all shapes and up to twelve
-// slab lengths on 90 lattices of 1 .. 16 million sites and checked on 130 others: the choice is 0.6% off the
-// fastest in the mean, 6% at worst; with STEP in their place it was 1.7% and 21% (5 x 2000 x 300 sites, 8 x 32 tiles
-// taken at 146 us where 12 x 32 take 121).  The same fit gained nothing for float.  A build may define
-// its own lists (one shape per precision for a quick build, say) before this header.
+// cubes of 40 .. 256 sites.  STEP_FULL is fitted to the times of all shapes and up to twelve slab
+// lengths on 90 lattices of 1 .. 25 million sites and checked on 130 others.  Double: the choice is 0.4%
+// off the fastest in the mean, 6% at worst; with STEP in its place it was 1.7% and 21% (5 x 2000 x 300
+// sites, 8 x 32 tiles taken at 146 us where 12 x 32 take 121).  Float: 1.2% and 13%; it was 1.8% and 25%.
+// Two blocks on a CU wait for memory together: the second float shape's price is for whole tiles, and
+// less for those of which the lattice uses a part (launch_cost).  A build may define its own lists (one
+// shape per precision for a quick build, say) before this header.
 #pragma once
 
 #ifndef SKYR_SHAPES_F64
 #define SKYR_SHAPES_F64(X) \
-    X(4, 4, 1, 16, 1, 1.0, 1.6, 1.65) X(4, 4, 1, 32, 1, 1.02, 1.51, 1.45) X(6, 2, 2, 32, 1, 0.95, 2.17, 1.95)
+    X(4, 4, 1, 16, 1, 1.0, 1.6, 1.8) X(4, 4, 1, 32, 1, 1.02, 1.51, 1.58) X(6, 2, 2, 32, 1, 0.95, 2.17, 2.2)
 #endif
 #ifndef SKYR_SHAPES_F32
 #define SKYR_SHAPES_F32(X) \
-    X(8, 4, 1, 32, 1, 1.0, 1.5, 1.5) X(6, 2, 2, 32, 2, 2.0, 1.3, 2.2) X(12, 4, 1, 32, 1, 0.9, 2.0, 2.0)
+    X(8, 4, 1, 32, 1, 1.0, 1.5, 1.7) X(6, 2, 2, 32, 2, 2.0, 1.3, 2.9) X(12, 4, 1, 32, 1, 0.9, 2.0, 2.0)
 #endif
 
 namespace skyr {

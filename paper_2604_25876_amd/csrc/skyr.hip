@@ -176,13 +176,21 @@ static void default_tile(const skyr_lattice* lat, skyr_precision prec, int& v_ou
 // no launch has more blocks than every workspace (and the fixed scratch) has records for
 constexpr int kMaxBlocks = 4084;
 
-static double launch_cost(skyr_precision prec, int v, int xc, long long blocks)
+static double launch_cost(const skyr_lattice* lat, const Launch& L)
 {
-    const Shape& sh = shape_of(prec, v);
+    const Shape& sh = L.shape;
+    const int blocks = L.blocks();
     const bool pair = sh.per_cu > 1 && blocks > kCUs;
-    const long long per_round = (long long)kCUs * (pair ? sh.per_cu : 1);
-    const long long rounds = (blocks + per_round - 1) / per_round;
-    return (double)rounds * (rounds > 1 ? kMultiRoundCost : 1.0) * (xc + 6) * (pair || rounds > 1 ? sh.step_full : sh.step);
+    const int per_round = kCUs * (pair ? sh.per_cu : 1);
+    const int rounds = (blocks + per_round - 1) / per_round;
+    double step = pair || rounds > 1 ? sh.step_full : sh.step;
+    if (pair) {
+        // the part of its tiles that the lattice fills, 0.8 at least (one row of twelve: 84 us a sweep of
+        // 900 x 5 x 700 sites; whole tiles on 770 x 37 x 665: 440 us, and 338 with one block on a CU)
+        const double tiles = (double)L.tiles_y * L.tiles_z * sh.oy() * sh.oz();
+        step *= std::max(0.8, (double)(lat->n[1] - 4) * (lat->n[2] - 4) / tiles);
+    }
+    return rounds * (rounds > 1 ? kMultiRoundCost : 1.0) * (L.xchunk + 6) * step;
 }
 
 // the even splits of nx planes into 1, 2, ... slabs: next_split gives the slab length of the next
@@ -197,13 +205,13 @@ static int next_split(int nx, int xc)
 static Launch default_launch(const skyr_lattice* lat, skyr_precision prec, int v0, int xc0)
 {
     Launch best = plan_with(lat, prec, v0, xc0);
-    double least = best.blocks() <= kMaxBlocks ? launch_cost(prec, v0, xc0, best.blocks()) : INFINITY;
+    double least = best.blocks() <= kMaxBlocks ? launch_cost(lat, best) : INFINITY;
     const int nx = lat->n[0] - 4;
     for (int v = 0; v < shape_count(prec); ++v)
         for (int xc = nx; xc > 0; xc = next_split(nx, xc)) {
             const Launch L = plan_with(lat, prec, v, xc);
             if (L.blocks() > kMaxBlocks) break;
-            const double c = launch_cost(prec, v, xc, L.blocks());
+            const double c = launch_cost(lat, L);
             if (c < least * (1.0 - 1e-9)) {
                 least = c;
                 best = L;
