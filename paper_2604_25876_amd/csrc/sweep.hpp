@@ -411,46 +411,51 @@ template <int CTRL> __device__ __forceinline__ double dpp_f64(double v)
     const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
-// The stages of a wave's sums after the first: lanes 2 away, 8 and 4 away within a row of 16 (turns of
-// the row: lanes 8 apart being equal after the first turn, 4 below is 4 above), then rows and halves
-// (a swap of two copies' rows leaves one's in one copy and the other's in the other).  The order is
-// that of wave_total and wave_totals alike: a sum does not depend on which of them formed it.  (With
-// the swaps first the block ends took longer: 40^3 double 5800 us for 300 steps against 5760.)
-template <bool MAX> __device__ __forceinline__ double wave_stages(double v)
+// The last stages of a wave's sums: the lanes 16 and 32 away (a swap of two copies' rows or halves
+// leaves one's in one copy and the other's in the other).  (With these stages first the block ends took
+// longer: 40^3 double 5800 us for 300 steps against 5760.)
+template <bool MAX> __device__ __forceinline__ double wave_rows(double v)
 {
-    const auto add = [](double a, double b) { return MAX ? fmax(a, b) : a + b; };
-    v = add(v, dpp_f64<0x4e>(v));   // quad lanes 2, 3, 0, 1
-    v = add(v, dpp_f64<0x128>(v));  // turned by 8 lanes of 16
-    v = add(v, dpp_f64<0x124>(v));  // by 4
     const auto halves = [&](auto swap) {
         const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
         const auto lo = swap((unsigned)u), hi = swap((unsigned)(u >> 32));
         const double x = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
         const double y = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
-        return add(x, y);
+        return MAX ? fmax(x, y) : x + y;
     };
     v = halves([](unsigned u) { return __builtin_amdgcn_permlane16_swap(u, u, false, false); });
-    v = halves([](unsigned u) { return __builtin_amdgcn_permlane32_swap(u, u, false, false); });
-    return v;
+    return halves([](unsigned u) { return __builtin_amdgcn_permlane32_swap(u, u, false, false); });
 }
-// the sum (maximum) of v over the wave, in every lane
+// The sum (maximum) of v over the wave, in every lane, in a fixed order: lanes 1 and 2 away, then (the
+// sums of all lanes of a quad being equal) the mirrored lanes of 8 and 16, then 16 and 32 away.
 template <bool MAX> __device__ __forceinline__ double wave_total(double v)
 {
-    const double w = dpp_f64<0xb1>(v);  // quad lanes 1, 0, 3, 2
-    return wave_stages<MAX>(MAX ? fmax(v, w) : v + w);
+    const auto add = [](double a, double b) { return MAX ? fmax(a, b) : a + b; };
+    v = add(v, dpp_f64<0xb1>(v));   // quad lanes 1, 0, 3, 2
+    v = add(v, dpp_f64<0x4e>(v));   // quad lanes 2, 3, 0, 1
+    v = add(v, dpp_f64<0x141>(v));  // mirrored in 8 lanes
+    v = add(v, dpp_f64<0x140>(v));  // mirrored in 16 lanes
+    return wave_rows<MAX>(v);
 }
 
-// a and b summed over the wave: a in the even lanes, b in the odd ones from the first stage on (two
-// sums for little more than one; every later stage goes an even number of lanes); the even lanes end
-// with a's, all with b's total
+// a and b summed over the wave (two sums for little more than one), every lane ending with both: a in
+// the even lanes, b in the odd ones from the first stage on, every later stage an even number of lanes
+// away.  The row is turned by 4 and by 8 lanes where wave_total mirrors it: quad 1 then adds quads 0 and
+// 1, and to them quads 2 and 3, as wave_total does, so that a sum is the same from either.
 __device__ __forceinline__ void wave_totals(double& a, double& b)
 {
     const bool odd = threadIdx.x & 1;
-    const double v = wave_stages<false>((odd ? b : a) + dpp_f64<0xb1>(odd ? a : b));
-    const unsigned long long w = __builtin_bit_cast(unsigned long long, v);
-    a = v;
-    b = __builtin_bit_cast(double, ((unsigned long long)__builtin_amdgcn_readlane((unsigned)(w >> 32), 1) << 32) |
-                                       (unsigned)__builtin_amdgcn_readlane((unsigned)w, 1));
+    double v = (odd ? b : a) + dpp_f64<0xb1>(odd ? a : b);
+    v += dpp_f64<0x4e>(v);
+    v += dpp_f64<0x124>(v);
+    v += dpp_f64<0x128>(v);
+    const unsigned long long w = __builtin_bit_cast(unsigned long long, wave_rows<false>(v));
+    const auto lane = [&](int i) {
+        return __builtin_bit_cast(double, ((unsigned long long)__builtin_amdgcn_readlane((unsigned)(w >> 32), i) << 32) |
+                                              (unsigned)__builtin_amdgcn_readlane((unsigned)w, i));
+    };
+    a = lane(4);
+    b = lane(5);
 }
 // the largest of the non-negative v over the wave, in every lane
 __device__ __forceinline__ double wave_most(double v) { return wave_total<true>(v); }
