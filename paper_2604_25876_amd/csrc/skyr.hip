@@ -167,12 +167,12 @@ static void default_tile(const skyr_lattice* lat, skyr_precision prec, int& v_ou
 // kMinChunk) stays what skyr_get_tile reports; the launch may take another shape and shorter
 // slabs, since field values do not depend on either.  A block marches xc + 4 planes and pays for
 // about two more (its first loads, its sums); a launch of r rounds of the chip takes r (xc + 6)
-// times the time of a step of its shape, 15% more when r > 1.  With the shapes' step times this picks
-// within 1.2% of the fastest of all (shape, slab length) pairs, measured on cubes of 40 .. 256
-// sites in both precisions (lattices of other proportions: shapes.hpp): one round with as many slabs as it holds, where the lattice is small
-// enough.  40^3: 2-plane slabs, 108-162 blocks, 17.5 us a sweep (19-21 when the pairs were measured,
-// before the ends of blocks got shorter) against 42-43.5 with the default tile's 18 blocks; 96^3: 31 / 39 us (float / double) against 44 / 47; 128^3 float 41 against 44;
-// 256^3 double on 8 x 32 tiles 451 against 478.
+// times the time of a step of its shape, 15% more when r > 1: one round with as many slabs as it
+// holds, where the lattice is small enough.  Against the fastest of all (shape, slab length) pairs on
+// cubes of 128, 151, 176, 200, 224 (float) and 256 sites: the fastest, but for 151^3 double (2-4% behind) and
+// 200^3 float (5%); lattices of other proportions: shapes.hpp.  40^3: 2-plane slabs, 108-162 blocks,
+// 17.4 us a sweep against 42-43.5 with the default tile's 18 blocks; 96^3: 31 / 39 us (float / double)
+// against 44 / 47; 128^3 float 41 against 44; 256^3 double on 8 x 32 tiles 451 against 478.
 // no launch has more blocks than every workspace (and the fixed scratch) has records for
 constexpr int kMaxBlocks = 4084;
 
